@@ -33,7 +33,7 @@ _STATUS = {0: "OK", -1: "INVAL", -2: "NOMEM", -3: "EXISTS", -4: "NOTFOUND", -5: 
 
 LIB_PATH = os.environ.get("PLORA_LIB") or os.path.join(os.path.dirname(os.path.abspath(__file__)), "libplora.so")
 if not os.path.exists(LIB_PATH):
-    raise ImportError("libplora.so is not built: run `python -m paper_2512_20210_amd.build` "
+    raise ImportError("libplora.so is not built: run `python paper_2512_20210_amd/build.py` "
                       "(or __graft_entry__.build()); there is no fallback implementation")
 lib = C.CDLL(LIB_PATH)
 
