@@ -240,6 +240,9 @@ int plora_pool_stats(plora_pool* pool, plora_stats* out);
  * many such blocks (prefill); other batches (decode: a hot adapter or two) cut them into items of 16
  * tokens for the ordinary kernel instead (0 = always).  "mfma_cols_max_group" (default 32): in a
  * batch of the first kind, a group's last <= this many tokens still go as 16-token items.
+ * "panel_min_tiles_shrink" (>= -1, default 32): shrink cuts the large adapter groups of a batch into tiles of up to 64
+ * tokens x 64 rows of A that a whole workgroup shares when the batch has at least this many of them (prefill) and
+ * every d_in of the pool is a multiple of 64; otherwise into items of 32 x 32 (-1 = never, 0 = whenever there is one).
  * "panel_half_max_workgroups" (>= 0, default 8192): a launch of that kernel with at most this many
  * workgroups of 512 columns is issued with one workgroup per 256 columns instead (twice as many, each
  * half as long; v is then read twice as often), which is faster while the launch is too short to hide

@@ -16,6 +16,9 @@ constexpr int kMfmaTokCols = 16;        // items of at most this many tokens tak
 constexpr int kMfmaColsMaxGroup = 32;   // panel batches: groups (or last blocks of groups) of at most this many
                                         // tokens are cut into column-split items (default of an option)
 constexpr int kMfmaRows = 32;           // rows of A per matrix-core shrink item
+constexpr int kPanelTokS = 64;          // tokens per panel shrink item
+constexpr int kPanelRowsS = 64;         // rows of A per panel shrink item
+constexpr int kPanelKS = 64;            // k-values per step of a panel shrink item: d_in is a multiple of it
 constexpr int kMfmaCols = 128;          // columns of B per matrix-core expand pass
 constexpr int kPtWindow = 1024;         // page-table entries a shrink item may stage in LDS
 constexpr int kMaxRank = 512;           // rows of B an expand item may stage page pairs for (4 KiB of LDS)
@@ -27,7 +30,7 @@ constexpr int kXcds = 8;                // consecutive workgroups go to consecut
 // One wavefront's worth of work, self-contained so that a wavefront needs a single 32-byte read
 // before it can start fetching page-table entries, activations and weights.
 struct ItemRec {
-  int16_t kind;    // -1 = padding (nothing to do), 0 = vector-ALU item, 1 = matrix-core item; + kItemOnce if no
+  int16_t kind;    // -1 = padding (nothing to do), 0 = vector-ALU item, 1 = matrix-core item, 2 = panel shrink item; + kItemOnce if no
                    // other item of the batch reads this item's weights (they are then fetched with streaming loads)
   int16_t ntok;    // tokens of the item
   int16_t rank;    // rank of the adapter (0 = tokens without adapter: shrink only clears v)
@@ -62,7 +65,7 @@ struct LaunchArgs {
   int32_t log2_page;
   int32_t v_stride;       // = max_rank
   int32_t slot_fastest;   // 1: grid = (slots, items, chunks); 0: grid = (items, chunks, slots); 2 (expand): (chunks, items, slots)
-  int32_t pad;
+  int32_t n_slots;        // of the launch (read by k_shrink_panel)
 };
 
 // One launch that does shrink and then expand over a few slots (plora_delta on small calls): workgroup w
@@ -112,14 +115,14 @@ struct ScatterRuns {
   int32_t phys_page[kScatterRuns];
 };
 
-enum LaunchMode { kModeBlocks = 0, kModeCoop = 1, kModeDeep = 2, kModePanel = 2, kModePanelHalf = 3 };
+enum LaunchMode { kModeBlocks = 0, kModeCoop = 1, kModeDeep = 2, kModePanel = 2, kModePanelHalf = 3, kModeShrinkPanel = 3 };
 
 // Launchers (plora_kernels.hip).  Both take a list of blocks of 4 records (one matrix-core item +
 // 3 padding records, or up to 4 vector-ALU items) and run one 256-thread workgroup per block, slot
 // and (expand) 512-column chunk.  kModeCoop: the list holds vector-ALU records only and every record
 // gets a 256-thread workgroup whose four wavefronts share the record's work (for calls too small to
 // fill the machine); kModeDeep (shrink): blocks, two runs in flight per matrix-core item; kModePanel
-// (expand): matrix-core blocks only, B stationary in LDS; kModePanelHalf: the same with one workgroup
+// (expand): matrix-core blocks only, B stationary in LDS; kModeShrinkPanel (shrink): blocks with panel items among them; kModePanelHalf: the same with one workgroup
 // per 256 columns instead of 512 (for launches of few workgroups).  Grid: (n_items, chunks, n_slots), or (n_slots, n_items, chunks) when
 // a.slot_fastest is set: consecutive workgroups go to consecutive XCDs, so with a slot count that
 // is a multiple of 8 every slot then lives on one XCD (its x, v and y rows meet in one L2) and all

@@ -707,6 +707,194 @@ __device__ __forceinline__ void shrink_mfma4_body(const LaunchArgs& a, const Ite
   }
 }
 
+// shrink, panel item (batches with many large groups: prefill): up to 64 rows of A x up to 64 tokens by a workgroup
+// whose four wavefronts share every tile, which goes from memory to LDS without a stop in registers.
+// What bounds it: the split item above (32 x 32) asks the CU's L1 for 2.5 KiB per 1024 products, and x comes back from
+// the last-level cache once per 32 rows of A and slot: a prefill of 5,120 tokens through q, k, v, o
+// (4096 -> 4096, ranks 8 .. 128) asked L1 for 644 MB, 250 MB of them past L2, and took 53.5 us (mean of three
+// batches).  The larger tile asks for 358 MB; with the slots of a token tile side by side on one XCD (k_shrink_panel)
+// x is fetched once for q, k and v: 36.5 us.  16,384 tokens through a 13B-shaped layer: 475 -> 376 us.  Not taken:
+// the tile through registers (45 - 49 us: a wavefront's step becomes load, LDS write, barrier, LDS read), 128 rows of
+// A (40: the few long workgroups of rank 128 decide), 32 tokens (43), 128 k-values a step (39, and two workgroups
+// per CU), operands straight from memory without LDS (65: 64-byte pieces of a row cost L1 as much as lines).
+constexpr int kSpTok = kPanelTokS, kSpRows = kPanelRowsS, kSpK = kPanelKS;
+constexpr int kSpRowB = 2 * kSpK;                          // bytes of a tile row
+constexpr int kSpLds = 3 * (kSpTok + kSpRows) * kSpRowB;   // 48 KiB: three workgroups fit a CU
+static_assert(kSpLds >= 4 * 2 * kSmRows * kSmPitch, "k_shrink_panel runs split items in the same space");
+static_assert(kSpTok == 64 && kSpRows == 64 && kSpK == 64, "the wavefronts' parts of a tile");
+typedef __attribute__((address_space(3))) void lds_void;
+__device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(uintptr_t)(const lds_void*)p; }
+// 16 bytes per lane from memory into LDS at dst + 16 * lane (dst: a uniform LDS address).
+// In assembly because the compiler makes every later LDS read wait for all such loads, also those into other stages;
+// here a stage is waited for with wait_loads and a barrier.  (No output registers: nothing is in flight but LDS bytes.
+// No other instruction of these kernels reads m0.)
+template <bool NTW>
+__device__ __forceinline__ void load_to_lds(const uint8_t* src, uint32_t dst) {
+  if constexpr (NTW) asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" : : "v"(src), "s"(dst) : "memory");
+  else asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {  // until at most N of the wavefront's vector memory accesses are in flight
+  static_assert(N >= 0 && N < 64, "six bits");
+  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
+}
+
+// NRT: row tiles of 16 that are held (ranks up to 32 leave half of the tile out).  CONTIG: the adapter lies on
+// consecutive pages, its addresses advance like x's; else every load looks its page up.
+template <int DT, int NRT, bool NTW, bool CONTIG>
+__device__ __forceinline__ void shrink_panel_body(const LaunchArgs& a, const ItemRec it, const SlotRec sl,
+                                                  const uint8_t* __restrict__ x, float* __restrict__ v,
+                                                  uint8_t* lds, const int32_t* lds_pt, const int32_t* lds_tok,
+                                                  uint64_t base, uint32_t win0, int nrows) {
+  constexpr int EB = 2;
+  constexpr int kRows = 16 * NRT;                          // rows of A in the tile: 32 or 64
+  constexpr int kWl = kRows / 32, kXl = kSpTok / 32;       // loads per wavefront and step, 8 rows x 128 bytes each
+  constexpr int kBuf = (kRows + kSpTok) * kSpRowB;
+  constexpr int S = kSpLds / kBuf;                         // stages: 3, or 4 of the smaller tile
+  constexpr bool kTall = NRT == 2;                         // the wavefronts' parts: four over the tokens, else two by two
+  constexpr int kMt = kTall ? 1 : 2, kNt = 2;              // token and row tiles of 16 per wavefront
+  const int wave = wave_id(), lane = lane_id();
+  const int g = lane >> 4, c = lane & 15;
+  const int d_in = sl.d_in, vs = a.v_stride, lp = a.log2_page;
+  const uint64_t pmask = ((uint64_t)1 << lp) - 1;
+  const uint64_t rowb = (uint64_t)d_in * EB;
+  // The 16-byte piece p of tile row r lies at place p ^ ((r >> 1) & 7) of the row in LDS, so that the 16 lanes that
+  // read one operand piece of 16 rows hit all 64 banks once.
+  uint64_t wcur[kWl];        // this lane's pieces of A in the step that is fetched next: virtual offsets (CONTIG: in the slab)
+  const uint8_t* xcur[kXl];  // and of x: addresses
+#pragma unroll
+  for (int i = 0; i < kWl; ++i) {
+    const int r = (i * 4 + wave) * 8 + (lane >> 3);
+    wcur[i] = base + (uint64_t)imin(r, nrows - 1) * rowb + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+    if (CONTIG) wcur[i] += (uint64_t)(uint32_t)it.pt_off << lp;
+  }
+#pragma unroll
+  for (int i = 0; i < kXl; ++i) {
+    const int r = (i * 4 + wave) * 8 + (lane >> 3);
+    xcur[i] = x + (uint64_t)(uint32_t)lds_tok[r] * rowb + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+  }
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(lds));
+  auto fetch = [&](uint32_t buf) {  // the next step's tile: A, then x
+#pragma unroll
+    for (int i = 0; i < kXl; ++i) load_to_lds<false>(xcur[i], lds0 + buf + (kRows + (i * 4 + wave) * 8) * kSpRowB);
+#pragma unroll
+    for (int i = 0; i < kWl; ++i) {
+      const uint8_t* src;
+      if constexpr (CONTIG) src = a.slab + wcur[i];
+      else src = a.slab + ((uint64_t)(uint32_t)lds_pt[(uint32_t)(wcur[i] >> lp) - win0] << lp) + (wcur[i] & pmask);
+      load_to_lds<NTW>(src, lds0 + buf + ((i * 4 + wave) * 8) * kSpRowB);
+    }
+#pragma unroll
+    for (int i = 0; i < kXl; ++i) xcur[i] += kSpRowB;
+#pragma unroll
+    for (int i = 0; i < kWl; ++i) wcur[i] += kSpRowB;
+  };
+  const int rw = kTall ? 0 : (wave & 1) * (kRows / 2), tw = kTall ? wave * 16 : (wave >> 1) * (kSpTok / 2);  // this wavefront's part
+  const int o0 = c * kSpRowB + ((g ^ ((c >> 1) & 7)) << 4), o1 = c * kSpRowB + (((4 + g) ^ ((c >> 1) & 7)) << 4);
+  f32x4 sum[kMt][kNt];
+#pragma unroll
+  for (int mt = 0; mt < kMt; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < kNt; ++nt) sum[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto next = [&](uint32_t o) { return o + kBuf == S * kBuf ? 0u : o + kBuf; };
+  const int n = d_in / kSpK;  // steps; the host takes panel items only where every d_in is a whole number of them
+  uint32_t ow = 0, ord = 0;   // the stages written and read next
+  const int pre = imin(S - 1, n);
+  for (int i = 0; i < pre; ++i) { fetch(ow); ow = next(ow); }
+  // The sums of 16 steps are collected at a time: rounding errors stay those of short chains (the split
+  // items' chains are d_in / 128 products of 32 terms long; here 16 per half step).
+  for (int i0 = 0; i0 < n; i0 += 16) {
+    const int i1 = imin(n, i0 + 16);
+    f32x4 acc[2][kMt][kNt];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int mt = 0; mt < kMt; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < kNt; ++nt) acc[h][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = i0; i < i1; ++i) {
+      // The step's stage has arrived (this wavefront's loads, then everybody's: barrier), and every wavefront has
+      // read the stage of step i - 1, which the loads of step i + S - 1 now overwrite.
+      if (i + S - 1 <= n) wait_loads<(S - 2) * (kWl + kXl)>(); else wait_loads<0>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      uint4 wo[2][kNt], xo[2][kMt];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int t = 0; t < kMt; ++t) xo[h][t] = *reinterpret_cast<const uint4*>(lds + ord + (kRows + tw + 16 * t) * kSpRowB + (h ? o1 : o0));
+#pragma unroll
+        for (int t = 0; t < kNt; ++t) wo[h][t] = *reinterpret_cast<const uint4*>(lds + ord + (rw + 16 * t) * kSpRowB + (h ? o1 : o0));
+      }
+      ord = next(ord);
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + S - 1 < n) { fetch(ow); ow = next(ow); }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int mt = 0; mt < kMt; ++mt)
+#pragma unroll
+          for (int nt = 0; nt < kNt; ++nt) acc[h][mt][nt] = mfma16<DT>(xo[h][mt], wo[h][nt], acc[h][mt][nt]);
+      // (the products wait for the operands, so this wavefront's LDS reads are done before it reaches the next barrier)
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int mt = 0; mt < kMt; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < kNt; ++nt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[mt][nt][e] += acc[0][mt][nt][e] + acc[1][mt][nt][e];
+  }
+#pragma unroll
+  for (int mt = 0; mt < kMt; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < kNt; ++nt) {
+      const int row = rw + 16 * nt + c;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int ti = tw + 16 * mt + 4 * g + e;
+        if (row < nrows && ti < it.ntok) v[(int64_t)lds_tok[ti] * vs + it.j0 + row] = sum[mt][nt][e];
+      }
+    }
+}
+
+template <int DT>
+__device__ __forceinline__ void shrink_panel_item(const LaunchArgs& a, const ItemRec it, const SlotRec sl,
+                                                  const uint8_t* __restrict__ x, float* __restrict__ v, uint8_t* lds,
+                                                  int32_t* lds_pt, int32_t* lds_tok) {
+  constexpr int EB = 2;
+  const int r = it.rank, lp = a.log2_page, vs = a.v_stride;
+  const int nrows = imin(kSpRows, r - it.j0);
+  const uint64_t rowb = (uint64_t)sl.d_in * EB;
+  const uint64_t base = (uint64_t)r * EB * (uint64_t)sl.cum + (uint64_t)it.j0 * rowb;
+  const uint32_t win0 = (uint32_t)(base >> lp);
+  const bool contig = item_contig(it);
+  if (!contig) {
+    const uint32_t win_n = (uint32_t)((base + (uint64_t)nrows * rowb - 1) >> lp) - win0 + 1;
+    const int32_t* ptg = a.pt + it.pt_off + win0;
+    for (uint32_t i = threadIdx.x; i < win_n; i += 256) lds_pt[i] = ptg[i];
+  }
+  const int32_t* perm = a.perm + it.tok[0];
+  if (threadIdx.x < kSpTok) lds_tok[threadIdx.x] = perm[imin((int)threadIdx.x, it.ntok - 1)];
+  __syncthreads();
+  if (it.j0 == 0) {  // clear v[t, r .. v_stride) for the item's tokens
+    for (int i = wave_id(); i < it.ntok; i += 4) {
+      const int64_t t = lds_tok[i];
+      for (int j = r + lane_id(); j < vs; j += kWave) v[t * vs + j] = 0.f;
+    }
+  }
+  if (nrows > 32) {
+    if (!contig) shrink_panel_body<DT, 4, false, false>(a, it, sl, x, v, lds, lds_pt, lds_tok, base, win0, nrows);
+    else if (item_once(it)) shrink_panel_body<DT, 4, true, true>(a, it, sl, x, v, lds, lds_pt, lds_tok, base, win0, nrows);
+    else shrink_panel_body<DT, 4, false, true>(a, it, sl, x, v, lds, lds_pt, lds_tok, base, win0, nrows);
+  } else {
+    if (!contig) shrink_panel_body<DT, 2, false, false>(a, it, sl, x, v, lds, lds_pt, lds_tok, base, win0, nrows);
+    else if (item_once(it)) shrink_panel_body<DT, 2, true, true>(a, it, sl, x, v, lds, lds_pt, lds_tok, base, win0, nrows);
+    else shrink_panel_body<DT, 2, false, true>(a, it, sl, x, v, lds, lds_pt, lds_tok, base, win0, nrows);
+  }
+}
+
 // Splits 8 fp32 values into a high and a low 16-bit part: hi = round(v), lo = round(v - hi).
 template <int DT>
 __device__ __forceinline__ void split_hi_lo(const float* f, uint4& hi, uint4& lo) {
@@ -1130,6 +1318,38 @@ __global__ __launch_bounds__(256, kWgPerCu) void k_shrink(const LaunchArgs a, co
   shrink_valu_item<DT>(a, it, sl, x, v, lds_pt + wave * (kPtWindow / 4));
 }
 
+// The shrink of a batch with many large adapter groups (prefill): as k_shrink, with panel items (kind 2)
+// at the head of the list.
+template <int DT>
+__global__ __launch_bounds__(256, kWgPerCu) void k_shrink_panel(const LaunchArgs a, const SlotPtrs p) {
+  __shared__ __align__(16) uint8_t lds[kSpLds];
+  __shared__ int32_t lds_pt[kPtWindow], lds_tok[kSpTok];
+  auto tile = reinterpret_cast<uint8_t(*)[2][kSmRows * kSmPitch]>(lds);
+  // Workgroup i runs on XCD i % 8.  The workgroups of one block of the list and all slots of the call follow each
+  // other on one XCD: slots that read the same x (q, k, v) then meet its rows in that XCD's L2.  The grid is rounded
+  // up to whole rounds of 8 blocks.
+  const int xcd = blockIdx.x & (kXcds - 1), pair = blockIdx.x / kXcds;
+  const int q = pair % a.n_slots, blk = pair / a.n_slots * kXcds + xcd;
+  if (4 * blk >= a.n_items) return;
+  const SlotRec sl = a.slots[p.slot[q]];
+  const uint8_t* x = (const uint8_t*)p.a[q];
+  float* v = (float*)p.b[q];
+  const ItemRec first = load_item(a.items + (4 * blk));
+  if (item_kind(first) == 2) {
+    shrink_panel_item<DT>(a, first, sl, x, v, lds, lds_pt, lds_tok);
+    return;
+  }
+  if (item_kind(first) == 1) {
+    if (item_once(first)) shrink_mfma4_body<DT, true, 2>(a, first, sl, x, v, tile, lds_pt);
+    else shrink_mfma4_body<DT, false, 2>(a, first, sl, x, v, tile, lds_pt);
+    return;
+  }
+  const int wave = wave_id();
+  const ItemRec it = load_item(a.items + (4 * blk + wave));
+  if (it.kind < 0) return;
+  shrink_valu_item<DT>(a, it, sl, x, v, lds_pt + wave * (kPtWindow / 4));
+}
+
 // Expand: same block structure as shrink (one matrix-core item per workgroup, or up to 4
 // independent vector-ALU items, one per wavefront); the column chunk (512 columns) comes from the
 // grid.
@@ -1429,7 +1649,7 @@ __global__ __launch_bounds__(256, kWgPerCu) void k_delta_queue(const FusedArgs f
   LaunchArgs a;
   a.slab = f.slab; a.perm = f.perm; a.pt = f.pt; a.items = nullptr; a.slots = f.slots;
   a.elems_per_rank = f.elems_per_rank; a.n_items = 0; a.pad0 = 0; a.log2_page = f.log2_page; a.v_stride = f.v_stride;
-  a.slot_fastest = 0; a.pad = 0;
+  a.slot_fastest = 0; a.n_slots = 0;
   const int per_slot_e = f.n_e * f.chunks;
   const int total_s = f.n_s * f.n_slots;
   const int total = total_s + per_slot_e * f.n_slots;
@@ -1617,10 +1837,11 @@ hipError_t launch_shrink(int dtype, const LaunchArgs& a0, const SlotPtrs& p, int
   if (a0.n_items <= 0 || n_slots <= 0) return hipSuccess;
   if (!single && a0.n_items % 4) return hipErrorInvalidValue;  // blocks of 4 records
   // kModeDeep: as kModeBlocks with two runs in flight per matrix-core item (fp32 has no such items)
-  static const KernelFn table[3][3] = {{k_shrink<0, 1>, k_shrink<1, 1>, k_shrink<2, 1>},
+  static const KernelFn table[4][3] = {{k_shrink<0, 1>, k_shrink<1, 1>, k_shrink<2, 1>},
                                        {k_shrink_coop<0>, k_shrink_coop<1>, k_shrink_coop<2>},
-                                       {k_shrink<0, 2>, k_shrink<1, 2>, k_shrink<2, 1>}};
-  if (mode < 0 || mode > 2 || dtype < 0 || dtype > 2) return hipErrorInvalidValue;
+                                       {k_shrink<0, 2>, k_shrink<1, 2>, k_shrink<2, 1>},
+                                       {k_shrink_panel<0>, k_shrink_panel<1>, nullptr}};
+  if (mode < 0 || mode > 3 || dtype < 0 || dtype > 2 || !table[mode][dtype]) return hipErrorInvalidValue;
   LaunchArgs a = a0;
   const int per = single ? 1 : 4;  // records per workgroup
   const int n_blocks = a0.n_items / per;
@@ -1629,7 +1850,8 @@ hipError_t launch_shrink(int dtype, const LaunchArgs& a0, const SlotPtrs& p, int
     const int nb = n_blocks - first < step ? n_blocks - first : step;
     a.items = a0.items + per * first;
     a.n_items = per * nb;
-    const dim3 grid = a.slot_fastest ? dim3(n_slots, 1, nb) : dim3(nb, 1, n_slots);
+    const dim3 grid = mode == kModeShrinkPanel ? dim3((nb + kXcds - 1) / kXcds * kXcds * n_slots)
+                    : a.slot_fastest ? dim3(n_slots, 1, nb) : dim3(nb, 1, n_slots);
     launch(table[mode][dtype], grid, dim3(256), st, first == 0 ? e0 : nullptr, first + step >= n_blocks ? e1 : nullptr, a, p);
   }
   return hipGetLastError();

@@ -74,6 +74,7 @@ struct plora_batch {
   plora_pool* pool = nullptr;
   bool open = false;
   bool panel = false;  // expand: the matrix-core blocks go to the panel kernel
+  bool panel_shrink = false;       // shrink: the list holds panel items (kind 2)
   bool full_shrink_tiles = false;  // shrink: the matrix-core items average at least half a token tile
   hipStream_t stream = nullptr;
   int32_t n_tokens = 0, n_seg = 0, n_perm = 0;
@@ -132,6 +133,13 @@ struct plora_pool {
   int panel_min_blocks = 8;  // expand: a batch with at least this many 64-token blocks of large groups (prefill) sends its
                              // matrix-core blocks to the panel kernel; other batches cut every large group into
                              // column-split items (0 = never)
+  // shrink: a batch with at least this many panel tiles (64 tokens x 64 rows of A) uses them (0 = always, -1 = never).
+  // A panel item's chain is d_in / 64 steps against a split item's d_in / 256, so launches that do not fill the GPU
+  // lose: 512 tokens over 8 adapters, one layer in calls of 3 + 1 slots, 35 us against 26 (8 - 12 tiles), 1,024 tokens 39
+  // against 38, 2,048 tokens 40 against 40 (32 or more); 2,048 tokens of ranks 8 / 16 in calls of 4 slots 17 against 20,
+  // 5,120 tokens 37 against 53.
+  int panel_min_tiles_shrink = 32;
+  bool panel_shrink_fits = false;  // the page-table window holds the rows of a panel item
   int64_t panel_half_max_workgroups = 8192;  // expand: a panel launch of at most this many workgroups (of 512 columns) is
                                              // issued with one workgroup per 256 columns instead (0 = never)
   int batches_per_marker = 4;                      // record the marker once this many batches share it
@@ -334,12 +342,14 @@ int plora_pool_create(size_t page_bytes, uint32_t n_pages, const plora_layout* l
   const int elt = lay->dtype == PLORA_F32 ? 4 : 2;
   int64_t c = 0;
   int max_in = 0, max_out = 0, min_out = 1 << 30;
+  bool whole_steps = true;  // every d_in a whole number of a panel item's steps
   std::vector<SlotRec> slots;
   for (int s = 0; s < lay->n_slots; ++s) {
     const int32_t di = lay->d_in[s], dn = lay->d_out[s];
     if (di <= 0 || dn <= 0 || di % 8 || dn % 8) return PLORA_ERR_INVAL;
     slots.push_back(SlotRec{di, dn, c});
     c += (int64_t)di + dn;
+    whole_steps = whole_steps && di % kPanelKS == 0;
     max_in = std::max(max_in, di);
     max_out = std::max(max_out, dn);
     min_out = std::min(min_out, dn);
@@ -357,6 +367,7 @@ int plora_pool_create(size_t page_bytes, uint32_t n_pages, const plora_layout* l
   p->placement_only = (flags & PLORA_POOL_PLACEMENT_ONLY) != 0;
   p->dtype = lay->dtype; p->elt = elt; p->max_adapters = lay->max_adapters; p->max_rank = lay->max_rank;
   p->n_slots = lay->n_slots; p->slots = slots; p->C = c; p->max_d_out = max_out;
+  p->panel_shrink_fits = whole_steps && (uint64_t)kPanelRowsS * (uint64_t)max_in * elt / page_bytes + 8 <= (uint64_t)kPtWindow;
   p->min_chunks = (min_out + kWave * (16 / elt) - 1) / (kWave * (16 / elt));
   p->free_bits.assign(((size_t)n_pages + 63) / 64, ~(uint64_t)0);
   if (n_pages & 63) p->free_bits.back() = (((uint64_t)1 << (n_pages & 63)) - 1);
@@ -775,6 +786,11 @@ int plora_pool_set_option(plora_pool* p, const char* key, int64_t value) {
     p->panel_min_blocks = (int)value;
     return PLORA_OK;
   }
+  if (k == "panel_min_tiles_shrink") {
+    if (value < -1 || value > (1 << 30)) return PLORA_ERR_INVAL;
+    p->panel_min_tiles_shrink = (int)value;
+    return PLORA_OK;
+  }
   if (k == "panel_half_max_workgroups") {
     if (value < 0 || value > ((int64_t)1 << 40)) return PLORA_ERR_INVAL;
     p->panel_half_max_workgroups = value;
@@ -926,6 +942,17 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
       for (int32_t left = std::min(n - b0, kTokBlock); left > p->cols_max_group; left -= kMfmaTokE) ++panel_blocks;
   }
   b->panel = p->panel_min_blocks > 0 && panel_blocks >= p->panel_min_blocks;
+  auto shrink_on_matrix_cores = [&](const Adapter& a, int32_t n) {
+    return mfma_ok && p->mfma_min_tokens > 0 && (n >= p->mfma_min_tokens || (int64_t)n * a.rank >= p->mfma_min_work);
+  };
+  int64_t panel_tiles = 0;
+  for (int32_t u = 0; u < n_seg && p->panel_min_tiles_shrink >= 0 && p->panel_shrink_fits; ++u) {
+    const int32_t n = p->count[touched[u]];
+    const Adapter& a = p->ad[touched[u]];
+    if (shrink_on_matrix_cores(a, n))
+      panel_tiles += (int64_t)(n / kPanelTokS + (n % kPanelTokS > kMfmaTokS)) * ((a.rank + kPanelRowsS - 1) / kPanelRowsS);
+  }
+  b->panel_shrink = panel_tiles > 0 && panel_tiles >= p->panel_min_tiles_shrink;
   const int32_t cols_max_group = b->panel ? p->cols_max_group : kTokBlock;
   size_t n_pt_total = 0;
   int64_t mfma_shrink_items = 0, mfma_shrink_tokens = 0;
@@ -938,8 +965,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     const int32_t pt_off = a.contig ? a.pt[0] : (int32_t)n_pt_total;
     if (!a.contig) n_pt_total += a.pt.size();
     const int16_t rank = (int16_t)a.rank;
-    const bool mf_s = mfma_ok && p->mfma_min_tokens > 0 &&
-                      (n >= p->mfma_min_tokens || (int64_t)n * a.rank >= p->mfma_min_work);
+    const bool mf_s = shrink_on_matrix_cores(a, n);
     const bool mf_e = expand_on_matrix_cores(a, n);
     // Matrix-core items.  Large groups (prefill) are cut into blocks of kTokBlock tokens: a block is
     // the unit that is dealt to an XCD, and inside a block the shrink items go row group by row
@@ -951,8 +977,18 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
         double cost = 0.0;
         // the rows of A are read by one item only when the group is a single token tile
         const int16_t kind = (int16_t)((n <= kMfmaTokS ? 1 | kItemOnce : 1) | contig);
+        // panel items first: whole tiles of tokens, and a last one that is more than half full
+        int32_t bp = b0;
+        if (b->panel_shrink) bp += (b1 - b0) / kPanelTokS * kPanelTokS + ((b1 - b0) % kPanelTokS > kMfmaTokS ? (b1 - b0) % kPanelTokS : 0);
+        const int16_t pkind = (int16_t)((n <= kPanelTokS ? 2 | kItemOnce : 2) | contig);
+        for (int32_t j0 = 0; j0 < a.rank && bp > b0; j0 += kPanelRowsS)
+          for (int32_t t0 = b0; t0 < bp; t0 += kPanelTokS) {
+            const int16_t nt = (int16_t)std::min(kPanelTokS, bp - t0);
+            wl[0][1].items.push_back(ItemRec{pkind, nt, rank, (int16_t)j0, a.scale, pt_off, {start + t0, 0, 0, 0}});
+            cost += std::min(kPanelRowsS, a.rank - j0) + nt;
+          }
         for (int32_t j0 = 0; j0 < a.rank; j0 += kMfmaRows)
-          for (int32_t t0 = b0; t0 < b1; t0 += kMfmaTokS) {
+          for (int32_t t0 = bp; t0 < b1; t0 += kMfmaTokS) {
             const int16_t nt = (int16_t)std::min(kMfmaTokS, b1 - t0);
             ++mfma_shrink_items;
             mfma_shrink_tokens += nt;
@@ -1021,7 +1057,8 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     // workgroup, longest chains first.  Not needed when even one slot's ordinary launch is past its limit.
     lists[op][2].clear();
     const int64_t min_grid = op == 1 ? p->min_chunks : 1;  // workgroups per block of the list in the smallest launch
-    if (p->coop_max_workgroups[op] > 0 && (int64_t)(lists[op][0].size() / 4) * min_grid <= p->coop_max_workgroups[op]) {
+    if (!(op == 0 ? b->panel_shrink : b->panel) && p->coop_max_workgroups[op] > 0 &&
+        (int64_t)(lists[op][0].size() / 4) * min_grid <= p->coop_max_workgroups[op]) {
       std::vector<ItemRec>& all = wl[op][1].items;  // reused as scratch: the matrix-core records are arranged already
       all.clear();
       size_t pt_run = 0;
@@ -1140,7 +1177,6 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
   const int vec = 16 / p->elt;
   const int op = is_shrink ? 0 : 1;
   a.pad0 = 0;
-  a.pad = 0;
   // Launch classes: an expand launch has one grid dimension for the 512-column chunks, so slots with
   // different chunk counts go in launches of their own (no empty workgroups) ...; shrink has one class.
   std::pair<int, int>* order = p->run_order.data();  // (chunks, index within the call), stable by chunks
@@ -1182,6 +1218,7 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     }
     const int chunks = order[q0].first;
     q0 += nq;
+    a.n_slots = nq;
     // slots fastest when that keeps every slot on one XCD and all XCDs equally loaded; else the
     // items are the fastest dimension and (optionally) come dealt into XCD queues
     a.slot_fastest = p->slot_major[op] == 2 ? 2 : (p->slot_major[op] == 1 || (p->slot_major[op] < 0 && nq % kXcds == 0)) ? 1 : 0;
@@ -1213,7 +1250,7 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     const int panel_mode = panel && 2 * chunks <= 65535 &&
                                    (int64_t)nq * (b->n_heavy[op] / 4) * chunks <= p->panel_half_max_workgroups
                                ? kModePanelHalf : kModePanel;
-    const Part parts[2] = {{list, panel ? b->n_heavy[op] : n_all, panel ? panel_mode : coop ? kModeCoop : deep ? kModeDeep : kModeBlocks},
+    const Part parts[2] = {{list, panel ? b->n_heavy[op] : n_all, panel ? panel_mode : coop ? kModeCoop : is_shrink && b->panel_shrink ? kModeShrinkPanel : deep ? kModeDeep : kModeBlocks},
                            {list + b->n_heavy[op], panel ? n_all - b->n_heavy[op] : 0, kModeBlocks}};
     plora_pool::ProfRec rec{op, nullptr, nullptr};
     if (p->profiling) {
@@ -1258,7 +1295,7 @@ int plora_expand(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t n_s
 static int delta_in_one_launch(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t n_slots, const void* const* x,
                                float* const* v, void* const* y, plora_stream s) {
   if (p->fused_max_tasks <= 0 || n_slots > kMaxSlotsFused || (hipStream_t)s != b->stream || !b->d_queue) return 1;
-  if (b->panel && b->n_heavy[1] > 0) return 1;
+  if ((b->panel && b->n_heavy[1] > 0) || b->panel_shrink) return 1;
   {
     // a captured launch would be replayed with this call's counter targets: graphs take the two launches
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
