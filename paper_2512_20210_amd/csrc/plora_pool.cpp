@@ -82,6 +82,7 @@ struct plora_batch {
   std::vector<int32_t> perm, seg_adapter, seg_start;
   // staging (pinned) and device image
   uint8_t* h_img = nullptr;
+  uint8_t* hd_img = nullptr;  // h_img as the device sees it
   uint8_t* d_img = nullptr;
   size_t cap = 0;
   // offsets inside the image
@@ -159,7 +160,7 @@ struct plora_pool {
   int64_t mfma_min_work = 64, mfma_min_work_expand = 128;
   // launch geometry, [shrink, expand]
   int xcd_remap[2] = {1, 0};  // item-fastest launches take the lists dealt into XCD queues
-  hipStream_t aux = nullptr;  // pool-owned side stream that carries the batch images
+  hipStream_t aux = nullptr;  // pool-owned side stream that carries the large batch images
   std::vector<std::pair<int, int>> run_order;  // scratch of a shrink / expand call, n_slots entries (never grows)
   std::vector<float*> static_v;                // scratch of plora_delta_static, n_slots entries (never grows)
   // plora_delta on small calls: one launch whose workgroups take shrink and then expand tasks from a queue
@@ -215,6 +216,10 @@ int poll_ready(plora_pool* p, Adapter& a) {
   return 1;
 }
 
+// Batch images up to this size go by a kernel.  One projection of 16 tokens takes 24 us a step that way and 51 with the
+// side stream; steps with images near the limit measure alike (a prefill of 5,120 tokens 131 and 131 us, 161 and 183
+// when the step starts on an idle GPU), and above it the copy behind running kernels is as good.
+constexpr size_t kImageByKernel = (size_t)256 << 10;
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Records the marker on its stream if that has not happened yet.
@@ -1088,6 +1093,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
       off = align_up(off + lists[op][k].size() * sizeof(ItemRec), 256);
     }
   const size_t need = std::max<size_t>(off, 256);
+  bool fresh_queue = false;  // cleared on the side stream: this batch's image has to travel there as well
   if (need > b->cap) {
     const size_t cap = align_up(need + need / 2, 4096);
     if (p->placement_only) {
@@ -1099,8 +1105,10 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
       if (b->d_img) { (void)hipFree(b->d_img); b->d_img = nullptr; }
       b->cap = 0;
       HIP_TRY(hipHostMalloc((void**)&b->h_img, cap, hipHostMallocDefault));
+      HIP_TRY(hipHostGetDevicePointer((void**)&b->hd_img, b->h_img, 0));
       HIP_TRY(hipMalloc((void**)&b->d_img, cap));
       if (!b->d_queue) {
+        fresh_queue = true;
         HIP_TRY(hipMalloc((void**)&b->d_queue, kQueueWords * sizeof(uint32_t)));
         HIP_TRY(hipMemsetAsync(b->d_queue, 0, kQueueWords * sizeof(uint32_t), p->aux));  // ahead of the image copy below
       }
@@ -1125,11 +1133,21 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
   b->perm.resize(n_perm);
 
   if (!p->placement_only) {
-    // the image travels on the pool's side stream, so it overlaps kernels already queued on `stream`
-    if (!b->ev_img) HIP_TRY(hipEventCreateWithFlags(&b->ev_img, hipEventDisableTiming));
-    HIP_TRY(hipMemcpyAsync(b->d_img, b->h_img, need, hipMemcpyHostToDevice, p->aux));
-    HIP_TRY(hipEventRecord(b->ev_img, p->aux));
-    HIP_TRY(hipStreamWaitEvent(b->stream, b->ev_img, 0));
+    // A small image goes by a kernel on the batch's own stream; a large one on the pool's side stream, where it
+    // overlaps kernels already queued on `stream` (so does the first of a batch object, behind its cleared queue
+    // state, and that of a stream under capture, which has to stay out of the graph).
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool by_kernel = launch_copy_image && need <= kImageByKernel && !fresh_queue &&
+                           hipStreamIsCapturing(b->stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+    if (by_kernel) {
+      HIP_TRY(launch_copy_image(b->hd_img, b->d_img, need, b->stream));
+    } else {
+      (void)hipGetLastError();
+      if (!b->ev_img) HIP_TRY(hipEventCreateWithFlags(&b->ev_img, hipEventDisableTiming));
+      HIP_TRY(hipMemcpyAsync(b->d_img, b->h_img, need, hipMemcpyHostToDevice, p->aux));
+      HIP_TRY(hipEventRecord(b->ev_img, p->aux));
+      HIP_TRY(hipStreamWaitEvent(b->stream, b->ev_img, 0));
+    }
     for (int32_t i : touched) {
       Adapter& a = p->ad[i];
       if (a.copy_pending && poll_ready(p, a) == 0) HIP_TRY(hipStreamWaitEvent(b->stream, a.ev_ready, 0));

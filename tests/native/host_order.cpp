@@ -82,6 +82,11 @@ hipError_t launch_expand(int, const LaunchArgs& a, const SlotPtrs&, int, int, in
   fakehip::enqueue_kernel(st, [a, expect] { kernel_body(a, expect); });
   return hipSuccess;
 }
+// A batch image that goes by a kernel: read from the page-locked buffer when the stream reaches it, not before.
+hipError_t launch_copy_image(const void* src, void* dst, size_t bytes, hipStream_t st) {
+  fakehip::enqueue_kernel(st, [=] { std::memcpy(dst, src, bytes); });
+  return hipSuccess;
+}
 // The one-launch form reads both lists (and the same pages) on its stream.
 hipError_t launch_delta_queue(int, const FusedArgs& f, const FusedPtrs&, hipStream_t st, hipEvent_t, hipEvent_t) {
   auto expect = g_expect;
