@@ -115,14 +115,15 @@ struct ScatterRuns {
   int32_t phys_page[kScatterRuns];
 };
 
-enum LaunchMode { kModeBlocks = 0, kModeCoop = 1, kModeDeep = 2, kModePanel = 2, kModePanelHalf = 3, kModeShrinkPanel = 3 };
+enum LaunchMode { kModeBlocks = 0, kModeCoop = 1, kModeDeep = 2, kModePanel = 2, kModePanelHalf = 3, kModeShrinkPanel = 3, kModeLight = 4 };
 
 // Launchers (plora_kernels.hip).  Both take a list of blocks of 4 records (one matrix-core item +
 // 3 padding records, or up to 4 vector-ALU items) and run one 256-thread workgroup per block, slot
 // and (expand) 512-column chunk.  kModeCoop: the list holds vector-ALU records only and every record
 // gets a 256-thread workgroup whose four wavefronts share the record's work (for calls too small to
 // fill the machine); kModeDeep (shrink): blocks, two runs in flight per matrix-core item; kModePanel
-// (expand): matrix-core blocks only, B stationary in LDS; kModeShrinkPanel (shrink): blocks with panel items among them; kModePanelHalf: the same with one workgroup
+// (expand): matrix-core blocks only, B stationary in LDS; kModeShrinkPanel (shrink): blocks with panel items among them; kModeLight
+// (shrink, fp32): blocks without matrix-core items; kModePanelHalf: the same with one workgroup
 // per 256 columns instead of 512 (for launches of few workgroups).  Grid: (n_items, chunks, n_slots), or (n_slots, n_items, chunks) when
 // a.slot_fastest is set: consecutive workgroups go to consecutive XCDs, so with a slot count that
 // is a multiple of 8 every slot then lives on one XCD (its x, v and y rows meet in one L2) and all

@@ -501,7 +501,7 @@ __device__ __forceinline__ void expand_valu_item(const LaunchArgs& a, const Item
 }
 
 // ------------------------------------------------------------------------------------------
-// matrix-core items (bf16 / f16 only)
+// matrix-core items
 // ------------------------------------------------------------------------------------------
 // v_mfma_f32_16x16x32: lane l holds, of the M x K operand, row l%16 and the 8 K-values of group
 // l/16; of the K x N operand, column l%16 and the same 8 K-values; of the 16x16 result, column
@@ -512,6 +512,16 @@ __device__ __forceinline__ f32x4 mfma16(const uint4 a, const uint4 b, const f32x
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
   else
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+
+// fp32: v_mfma_f32_16x16x4 takes one value per lane, row (column) lane % 16 and K-value lane / 16.  Where a 16-bit
+// operand is 16 bytes of a row, four fp32 values, the four of both operands are fed to four such instructions in turn:
+// instruction e covers the K-values 4 g + e (g = lane / 16) of the piece, in both operands alike.
+__device__ __forceinline__ f32x4 mfma16_f32(const uint4 a, const uint4 b, f32x4 c) {
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
 }
 
 // shrink, matrix-core item: D[token, row] += X[token, k] * A[row, k] for 32 tokens x 32 rows, by a
@@ -530,7 +540,8 @@ template <int DT, bool NTW, int DEPTH, bool COH = false>
 __device__ __forceinline__ void shrink_mfma4_body(const LaunchArgs& a, const ItemRec it, const SlotRec sl,
                                                   const uint8_t* __restrict__ x, float* __restrict__ v,
                                                   uint8_t (*tile)[2][kSmRows * kSmPitch], int32_t* lds_pt) {
-  constexpr int EB = 2;
+  constexpr int EB = Elt<DT>::B, VEC = Elt<DT>::VEC;
+  constexpr int kRun = 8 * VEC;  // k-values of a run: 128 bytes of a row
 
   const int tid = threadIdx.x, wave = wave_id(), lane = tid & 63;
   const int g = lane >> 4, c = lane & 15;   // MFMA coordinates
@@ -566,8 +577,8 @@ __device__ __forceinline__ void shrink_mfma4_body(const LaunchArgs& a, const Ite
   }
   __syncthreads();
 
-  // this wavefront's quarter of the contraction, in runs of 64 k-values
-  const int nrun = (d_in + 63) >> 6;
+  // this wavefront's quarter of the contraction, in runs of kRun k-values
+  const int nrun = (d_in + kRun - 1) / kRun;
   const int per = (nrun + 3) >> 2;
   const int mine = (nrun - wave + 3) >> 2;  // runs wave, wave + 4, ...
 #define SM_RUN(i) ((i) * 4 + wave)
@@ -580,10 +591,10 @@ __device__ __forceinline__ void shrink_mfma4_body(const LaunchArgs& a, const Ite
 
   uint8_t* tw = tile[wave][0];
   uint8_t* tx = tile[wave][1];
-  // Loads of a run of 64 k-values into registers (always issued: callers clamp the run, so that the
+  // Loads of a run of kRun k-values into registers (always issued: callers clamp the run, so that the
   // compiler can count the loads in flight), their way into LDS, and the products from there.
   auto fetch = [&](int run, uint4 (&wq)[4], uint4 (&xq)[4]) -> bool {
-    const int k = run * 64 + lp8 * 8;
+    const int k = run * kRun + lp8 * VEC;
     const bool ok = k < d_in;  // past a ragged end the lane reads k = 0 and stages zeros
     const uint64_t kb = (uint64_t)(ok ? k : 0) * EB;
 #pragma unroll
@@ -606,6 +617,32 @@ __device__ __forceinline__ void shrink_mfma4_body(const LaunchArgs& a, const Ite
     }
   };
   auto multiply = [&]() {
+    if constexpr (DT == 2) {
+      // Tiles without tokens or rows are left out (fp32 products are what bounds an item of few adapters' groups).
+      // 16 products at a time, collected by additions: one chain over d_in / 4 products would have 2.6 times the
+      // error of the vector-ALU item's short ones (at d_in 2048 4.1e-7 of the 2-norm against 1.2e-7).
+      uint4 xo[2][2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) xo[t][h] = *reinterpret_cast<const uint4*>(tx + (16 * t + c) * kSmPitch + h * 64 + g * 16);
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt) {
+        if (16 * nt >= nrows) continue;  // uniform
+        uint4 wo[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) wo[h] = *reinterpret_cast<const uint4*>(tw + (16 * nt + c) * kSmPitch + h * 64 + g * 16);
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+          if (16 * mt >= it.ntok) continue;  // uniform
+          const f32x4 t0 = mfma16_f32(xo[mt][0], wo[0], f32x4{0.f, 0.f, 0.f, 0.f});
+          const f32x4 t1 = mfma16_f32(xo[mt][1], wo[1], f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[mt][nt][e] += t0[e] + t1[e];
+        }
+      }
+      return;
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       uint4 wo[2], xo[2];
@@ -614,10 +651,11 @@ __device__ __forceinline__ void shrink_mfma4_body(const LaunchArgs& a, const Ite
         wo[t] = *reinterpret_cast<const uint4*>(tw + (16 * t + c) * kSmPitch + h * 64 + g * 16);
         xo[t] = *reinterpret_cast<const uint4*>(tx + (16 * t + c) * kSmPitch + h * 64 + g * 16);
       }
+      if constexpr (DT != 2)
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
+        for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = mfma16<DT>(xo[mt], wo[nt], acc[mt][nt]);
+          for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = mfma16<DT>(xo[mt], wo[nt], acc[mt][nt]);
     }
   };
   if constexpr (DEPTH == 2) {
@@ -1079,6 +1117,80 @@ __device__ __forceinline__ void expand_mfma_cols_body(const LaunchArgs& a, const
   }
 }
 
+// The same for fp32, up to 16 tokens: a wavefront takes 64 columns, lane (g, c) the four from 4 c on.  Of 16 rows of B lane
+// group g loads rows 4 g .. 4 g + 3, 16 bytes per lane, and of v's operand row c the same four values; instruction
+// (s, e) multiplies row 4 g + s with column offset e, so nothing is transposed and a lane ends with four
+// consecutive columns of four tokens.  What bounds it: the vector-ALU item reads B again for every 4 tokens and
+// spends an instruction per product and token; 2,048 tokens (2048 -> 2048, q, k, v, o) took 55 us that way and take 35.
+template <bool NTW, bool COH>
+__device__ __forceinline__ void expand_mfma_cols_f32_body(const LaunchArgs& a, const ItemRec it, const SlotRec sl,
+                                                          const float* __restrict__ v, uint8_t* __restrict__ y,
+                                                          const int2* lds_pg, int chunk, uint64_t base, uint64_t rowb) {
+  const int wave = wave_id(), lane = lane_id();
+  const int g = lane >> 4, c = lane & 15;
+  const int r = it.rank, d_out = sl.d_out, vs = a.v_stride, lp = a.log2_page;
+  const uint32_t pmask = (1u << lp) - 1;
+  const int n0 = chunk * 256 + wave * 64;
+  if (n0 >= d_out) return;
+  const int n = n0 + 4 * c;
+  const bool ok = n < d_out;
+  const uint32_t lane_b = ok ? (uint32_t)((wave * 64 + 4 * c) * 4) : 0;
+  const int tc = a.perm[it.tok[0] + imin(c, it.ntok - 1)];
+  const float* vrow = v + (int64_t)tc * vs;
+  int64_t trow[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) trow[i] = __shfl(tc, g * 4 + i, 64);
+  const int nn = ok ? n : n0;
+  uint4 yq[4];  // requested now, used after the loop
+#pragma unroll
+  for (int i = 0; i < 4; ++i) yq[i] = ldy16(y + ((uint64_t)trow[i] * d_out + nn) * 4);
+  f32x4 acc[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto rows16 = [&](int jb, auto tail) {  // rows jb .. jb + 15 of B
+    constexpr bool kTail = decltype(tail)::value;
+    const int j4 = jb + 4 * g;
+    uint4 w[4];
+    float vf[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int j = kTail ? imin(j4 + s, r - 1) : j4 + s;
+      const uint64_t vo = base + (uint64_t)j * rowb;
+      const uint32_t inpage = ((uint32_t)vo & pmask) + lane_b;
+      const int2 pp = lds_pg[j];
+      const uint64_t pg = (uint64_t)(uint32_t)((inpage >> lp) ? pp.y : pp.x);
+      w[s] = ldw16<NTW>(a.slab + (pg << lp) + (inpage & pmask));
+      vf[s] = ld_v<COH>(vrow + j);
+    }
+    if (kTail) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        if (j4 + s >= r) { w[s] = make_uint4(0, 0, 0, 0); vf[s] = 0.f; }
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[s], __uint_as_float(w[s].x), acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[s], __uint_as_float(w[s].y), acc[1], 0, 0, 0);
+      acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[s], __uint_as_float(w[s].z), acc[2], 0, 0, 0);
+      acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[s], __uint_as_float(w[s].w), acc[3], 0, 0, 0);
+    }
+  };
+  int jb = 0;
+  for (; jb + 16 <= r; jb += 16) rows16(jb, std::false_type{});
+  if (jb < r) rows16(jb, std::true_type{});
+  if (!ok) return;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (g * 4 + i < it.ntok) {
+      float yf[4];
+      unpack<2>(yq[i], yf);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) yf[e] = __builtin_fmaf(it.scale, acc[e][i], yf[e]);
+      sty16(y + ((uint64_t)trow[i] * d_out + n) * 4, pack<2>(yf));
+    }
+  }
+}
+
 // Page pairs of every row's 1 KiB piece of the 512-column chunk, staged in LDS by all 256 threads
 // (a piece may straddle one page boundary).
 __device__ __forceinline__ void expand_stage_pages(const LaunchArgs& a, const ItemRec& it, int2* lds_pg, uint64_t base,
@@ -1101,15 +1213,20 @@ template <int DT, bool COH = false>
 __device__ __forceinline__ void expand_mfma_cols_item(const LaunchArgs& a, const ItemRec it, const SlotRec sl,
                                                       const float* __restrict__ v, uint8_t* __restrict__ y,
                                                       int2* lds_pg, int chunk) {
-  constexpr int EB = 2;
-  const int n0i = chunk * 512;
+  constexpr int EB = Elt<DT>::B;
+  const int n0i = chunk * (kWave * Elt<DT>::VEC);
   if (n0i >= sl.d_out) return;  // uniform over the workgroup
   const uint64_t rowb = (uint64_t)sl.d_out * EB;
   const uint64_t base = (uint64_t)it.rank * EB * ((uint64_t)sl.cum + (uint64_t)sl.d_in) + (uint64_t)n0i * EB;
   expand_stage_pages(a, it, lds_pg, base, rowb, EB);
   __syncthreads();
-  if (item_once(it)) expand_mfma_cols_body<DT, 1, true, COH>(a, it, sl, v, y, lds_pg, chunk, base, rowb);
-  else expand_mfma_cols_body<DT, 1, false, COH>(a, it, sl, v, y, lds_pg, chunk, base, rowb);
+  if constexpr (DT == 2) {
+    if (item_once(it)) expand_mfma_cols_f32_body<true, COH>(a, it, sl, v, y, lds_pg, chunk, base, rowb);
+    else expand_mfma_cols_f32_body<false, COH>(a, it, sl, v, y, lds_pg, chunk, base, rowb);
+  } else {
+    if (item_once(it)) expand_mfma_cols_body<DT, 1, true, COH>(a, it, sl, v, y, lds_pg, chunk, base, rowb);
+    else expand_mfma_cols_body<DT, 1, false, COH>(a, it, sl, v, y, lds_pg, chunk, base, rowb);
+  }
 }
 
 // expand, matrix-core item of 17 .. 64 tokens (batches with many large groups: prefill):
@@ -1294,10 +1411,11 @@ __device__ __forceinline__ void expand_panel_item(const LaunchArgs& a, const Ite
 // or up to 4 independent vector-ALU items, one per wavefront.  The matrix-core blocks come first in
 // the list, so their long dependent chains start first and the short items fill the machine around
 // and after them in the same launch.
-// DEPTH: runs of 64 k-values that a matrix-core item keeps in flight (1 or 2).
+// DEPTH: runs of 128 bytes of a row that a matrix-core item keeps in flight (1 or 2; 0: the list holds no such items
+// and the tiles' space is left to more workgroups).
 template <int DT, int DEPTH>
 __global__ __launch_bounds__(256, kWgPerCu) void k_shrink(const LaunchArgs a, const SlotPtrs p) {
-  __shared__ __align__(16) uint8_t tile[4][2][kSmRows * kSmPitch];  // [wavefront][A | x]
+  __shared__ __align__(16) uint8_t tile[DEPTH ? 4 : 1][2][DEPTH ? kSmRows * kSmPitch : 16];  // [wavefront][A | x]
   __shared__ int32_t lds_pt[kPtWindow];
   const int blk = a.slot_fastest ? blockIdx.z : blockIdx.x;
   const int q = a.slot_fastest ? blockIdx.x : blockIdx.z;
@@ -1305,7 +1423,7 @@ __global__ __launch_bounds__(256, kWgPerCu) void k_shrink(const LaunchArgs a, co
   const uint8_t* x = (const uint8_t*)p.a[q];
   float* v = (float*)p.b[q];
   const ItemRec first = load_item(a.items + (4 * blk));
-  if constexpr (DT != 2) {
+  if constexpr (DEPTH > 0) {
     if (item_kind(first) == 1) {
       if (item_once(first)) shrink_mfma4_body<DT, true, DEPTH>(a, first, sl, x, v, tile, lds_pt);
       else shrink_mfma4_body<DT, false, DEPTH>(a, first, sl, x, v, tile, lds_pt);
@@ -1373,11 +1491,9 @@ __global__ __launch_bounds__(256, kWgPerCu) void k_expand(const LaunchArgs a, co
   const float* v = (const float*)p.a[q];
   uint8_t* y = (uint8_t*)p.b[q];
   const ItemRec first = load_item(a.items + (4 * blk));
-  if constexpr (DT != 2) {
-    if (item_kind(first) == 1) {  // at most kMfmaTokCols tokens: larger items go to k_expand_panel
-      expand_mfma_cols_item<DT>(a, first, sl, v, y, lds_pg, chunk);
-      return;
-    }
+  if (item_kind(first) == 1) {  // at most kMfmaTokCols tokens: larger items go to k_expand_panel
+    expand_mfma_cols_item<DT>(a, first, sl, v, y, lds_pg, chunk);
+    return;
   }
   const int wave = wave_id();
   const ItemRec it = load_item(a.items + (4 * blk + wave));
@@ -1684,12 +1800,10 @@ __global__ __launch_bounds__(256, kWgPerCu) void k_delta_queue(const FusedArgs f
         int32_t* lds_pt = reinterpret_cast<int32_t*>(lds + 4 * 2 * kSmRows * kSmPitch);
         const ItemRec first = load_item(f.items_s + 4 * w);
         bool matrix = false;
-        if constexpr (DT != 2) {
-          if (item_kind(first) == 1) {
-            matrix = true;
-            if (item_once(first)) shrink_mfma4_body<DT, true, 2, true>(a, first, sl, x, v, tile, lds_pt);
-            else shrink_mfma4_body<DT, false, 2, true>(a, first, sl, x, v, tile, lds_pt);
-          }
+        if (item_kind(first) == 1) {
+          matrix = true;
+          if (item_once(first)) shrink_mfma4_body<DT, true, 2, true>(a, first, sl, x, v, tile, lds_pt);
+          else shrink_mfma4_body<DT, false, 2, true>(a, first, sl, x, v, tile, lds_pt);
         }
         if (!matrix) {
           const ItemRec it = load_item(f.items_s + 4 * w + wave);
@@ -1742,11 +1856,9 @@ __global__ __launch_bounds__(256, kWgPerCu) void k_delta_queue(const FusedArgs f
         int2* my_pg = reinterpret_cast<int2*>(lds);
         const ItemRec first = load_item(f.items_e + 4 * blk);
         bool matrix = false;
-        if constexpr (DT != 2) {
-          if (item_kind(first) == 1) {
-            matrix = true;
-            expand_mfma_cols_item<DT, true>(a, first, sl, v, y, my_pg, chunk);
-          }
+        if (item_kind(first) == 1) {
+          matrix = true;
+          expand_mfma_cols_item<DT, true>(a, first, sl, v, y, my_pg, chunk);
         }
         if (!matrix) {
           const ItemRec it = load_item(f.items_e + 4 * blk + wave);
@@ -1853,12 +1965,13 @@ hipError_t launch_shrink(int dtype, const LaunchArgs& a0, const SlotPtrs& p, int
   const bool single = mode == kModeCoop;  // one record per workgroup
   if (a0.n_items <= 0 || n_slots <= 0) return hipSuccess;
   if (!single && a0.n_items % 4) return hipErrorInvalidValue;  // blocks of 4 records
-  // kModeDeep: as kModeBlocks with two runs in flight per matrix-core item (fp32 has no such items)
-  static const KernelFn table[4][3] = {{k_shrink<0, 1>, k_shrink<1, 1>, k_shrink<2, 1>},
+  // kModeDeep: as kModeBlocks with two runs in flight per matrix-core item; kModeLight: no such items in the list
+  static const KernelFn table[5][3] = {{k_shrink<0, 1>, k_shrink<1, 1>, k_shrink<2, 1>},
                                        {k_shrink_coop<0>, k_shrink_coop<1>, k_shrink_coop<2>},
-                                       {k_shrink<0, 2>, k_shrink<1, 2>, k_shrink<2, 1>},
-                                       {k_shrink_panel<0>, k_shrink_panel<1>, nullptr}};
-  if (mode < 0 || mode > 3 || dtype < 0 || dtype > 2 || !table[mode][dtype]) return hipErrorInvalidValue;
+                                       {k_shrink<0, 2>, k_shrink<1, 2>, k_shrink<2, 2>},
+                                       {k_shrink_panel<0>, k_shrink_panel<1>, nullptr},
+                                       {nullptr, nullptr, k_shrink<2, 0>}};
+  if (mode < 0 || mode > 4 || dtype < 0 || dtype > 2 || !table[mode][dtype]) return hipErrorInvalidValue;
   LaunchArgs a = a0;
   const int per = single ? 1 : 4;  // records per workgroup
   const int n_blocks = a0.n_items / per;

@@ -216,6 +216,14 @@ int poll_ready(plora_pool* p, Adapter& a) {
   return 1;
 }
 
+// fp32 groups take matrix-core items from this many tokens on ...
+constexpr int kF32MinTokens = 16;
+// ... in shrink only if the batch has at least this many such items: an item's products alone are 28 us on its four
+// SIMDs at d_in 4096, so a few items are a longer chain than the vector-ALU items they replace (256 tokens over 64
+// adapters, 4 slots 4096 -> 4096 a call: 36 us a launch with vector-ALU items, 43 - 50 with 8 matrix-core items; 1,024
+// tokens in calls of 3 + 1 slots, about 40 items: 346 against 327 us on average and 275 against 363 at worst; 2,048
+// tokens of prefill 2048 -> 2048, 64 items or more: 107 against 36).
+constexpr int64_t kF32MinItems = 64;
 // Batch images up to this size go by a kernel.  One projection of 16 tokens takes 24 us a step that way and 51 with the
 // side stream; steps with images near the limit measure alike (a prefill of 5,120 tokens 131 and 131 us, 161 and 183
 // when the step starts on an idle GPU), and above it the copy behind running kernels is as good.
@@ -914,7 +922,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
   }
 
   // work items, grouped per adapter (tokens without adapter form one rank-0 group: shrink clears their v rows)
-  const bool mfma_ok = p->dtype != PLORA_F32;  // matrix-core items exist for the 16-bit element types
+  const bool half = p->dtype != PLORA_F32;  // the panel items, and the rules on a group's work, are for the 16-bit types
   ItemGroups(&wl)[2][2] = p->wl;               // [op][0 vector-ALU | 1 matrix-core]
   for (int op = 0; op < 2; ++op)
     for (int k = 0; k < 2; ++k) wl[op][k].clear();
@@ -933,8 +941,9 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
   constexpr int kTokBlock = 128;
   auto expand_on_matrix_cores = [&](const Adapter& a, int32_t n) {
     const int64_t r32 = ((int64_t)a.rank + 31) / 32 * 32;
-    return mfma_ok && p->mfma_min_tokens_expand > 0 &&
-           (n >= p->mfma_min_tokens_expand || (int64_t)n * a.rank * a.rank >= p->mfma_min_work_expand * r32);
+    if (p->mfma_min_tokens_expand <= 0) return false;
+    if (!half) return n >= std::min(p->mfma_min_tokens_expand, kF32MinTokens);
+    return n >= p->mfma_min_tokens_expand || (int64_t)n * a.rank * a.rank >= p->mfma_min_work_expand * r32;
   };
   // How the large groups' expand work is cut: a batch with many 64-token blocks (prefill) keeps them
   // (B is then staged once per 64 tokens) and runs them in the panel kernel; a batch with few
@@ -946,9 +955,19 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     for (int32_t b0 = 0; b0 < n; b0 += kTokBlock)
       for (int32_t left = std::min(n - b0, kTokBlock); left > p->cols_max_group; left -= kMfmaTokE) ++panel_blocks;
   }
-  b->panel = p->panel_min_blocks > 0 && panel_blocks >= p->panel_min_blocks;
+  b->panel = half && p->panel_min_blocks > 0 && panel_blocks >= p->panel_min_blocks;
+  // fp32: matrix-core shrink items only in a batch with many of them, see kF32MinItems (an explicit threshold below the
+  // default asks for them in any batch)
+  int64_t f32_items = p->mfma_min_tokens < kF32MinTokens ? kF32MinItems : 0;
+  for (int32_t u = 0; u < n_seg && !half; ++u) {
+    const int32_t n = p->count[touched[u]];
+    if (n >= kF32MinTokens)
+      f32_items += (int64_t)((n + kMfmaTokS - 1) / kMfmaTokS) * ((p->ad[touched[u]].rank + kMfmaRows - 1) / kMfmaRows);
+  }
   auto shrink_on_matrix_cores = [&](const Adapter& a, int32_t n) {
-    return mfma_ok && p->mfma_min_tokens > 0 && (n >= p->mfma_min_tokens || (int64_t)n * a.rank >= p->mfma_min_work);
+    if (p->mfma_min_tokens <= 0) return false;
+    if (!half) return f32_items >= kF32MinItems && n >= std::min(p->mfma_min_tokens, kF32MinTokens);
+    return n >= p->mfma_min_tokens || (int64_t)n * a.rank >= p->mfma_min_work;
   };
   int64_t panel_tiles = 0;
   for (int32_t u = 0; u < n_seg && p->panel_min_tiles_shrink >= 0 && p->panel_shrink_fits; ++u) {
@@ -957,7 +976,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     if (shrink_on_matrix_cores(a, n))
       panel_tiles += (int64_t)(n / kPanelTokS + (n % kPanelTokS > kMfmaTokS)) * ((a.rank + kPanelRowsS - 1) / kPanelRowsS);
   }
-  b->panel_shrink = panel_tiles > 0 && panel_tiles >= p->panel_min_tiles_shrink;
+  b->panel_shrink = half && panel_tiles > 0 && panel_tiles >= p->panel_min_tiles_shrink;
   const int32_t cols_max_group = b->panel ? p->cols_max_group : kTokBlock;
   size_t n_pt_total = 0;
   int64_t mfma_shrink_items = 0, mfma_shrink_tokens = 0;
@@ -1254,7 +1273,7 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     // matrix-core shrink items keep two runs of k-values in flight where that pays: token tiles that
     // are mostly full (prefill), or a long contraction
     bool deep = false;
-    if (is_shrink && !coop && p->dtype != PLORA_F32 && b->n_heavy[0] > 0) {
+    if (is_shrink && !coop && b->n_heavy[0] > 0) {
       int32_t max_in = 0;
       for (int q = 0; q < nq; ++q) max_in = std::max(max_in, p->slots[ptrs.slot[q]].d_in);
       // ... or a launch too small to hide the chain of an item's runs behind other workgroups
@@ -1268,7 +1287,8 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     const int panel_mode = panel && 2 * chunks <= 65535 &&
                                    (int64_t)nq * (b->n_heavy[op] / 4) * chunks <= p->panel_half_max_workgroups
                                ? kModePanelHalf : kModePanel;
-    const Part parts[2] = {{list, panel ? b->n_heavy[op] : n_all, panel ? panel_mode : coop ? kModeCoop : is_shrink && b->panel_shrink ? kModeShrinkPanel : deep ? kModeDeep : kModeBlocks},
+    const Part parts[2] = {{list, panel ? b->n_heavy[op] : n_all, panel ? panel_mode : coop ? kModeCoop : is_shrink && b->panel_shrink ? kModeShrinkPanel : deep ? kModeDeep
+                           : is_shrink && p->dtype == PLORA_F32 && b->n_heavy[0] == 0 ? kModeLight : kModeBlocks},
                            {list + b->n_heavy[op], panel ? n_all - b->n_heavy[op] : 0, kModeBlocks}};
     plora_pool::ProfRec rec{op, nullptr, nullptr};
     if (p->profiling) {
