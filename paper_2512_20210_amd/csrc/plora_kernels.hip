@@ -299,6 +299,44 @@ __device__ __forceinline__ void shrink_valu_chunk(const LaunchArgs& a, const uin
   }
 }
 
+// Two whole chunks (16-bit elements), requested together and added in turn: the sums of two calls of the above.
+template <int DT, int NT, int ROWS, bool NTW>
+__device__ __forceinline__ void shrink_valu_chunk2(const LaunchArgs& a, const uint8_t* __restrict__ x, const int64_t* tok,
+                                                   const int32_t* lds_pt, uint32_t win0, uint64_t base, uint64_t rowb,
+                                                   int nrows, int d_in, int k0, int k1, float (*acc)[NT]) {
+  static_assert(DT != 2, "packed products");
+  constexpr int EB = Elt<DT>::B, VEC = Elt<DT>::VEC;
+  const int lp = a.log2_page;
+  const uint64_t pmask = ((uint64_t)1 << lp) - 1;
+  uint4 xq[2][NT], wq[2][ROWS];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int k = (h ? k1 : k0) + lane_id() * VEC;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) xq[h][i] = ld16(x + ((uint64_t)tok[i] * d_in + k) * EB);
+#pragma unroll
+    for (int jj = 0; jj < ROWS; ++jj) {
+      const uint64_t voff = base + (uint64_t)imin(jj, nrows - 1) * rowb + (uint64_t)k * EB;
+      const uint64_t pg = (uint64_t)(uint32_t)lds_pt[(uint32_t)(voff >> lp) - win0];
+      wq[h][jj] = ldw16<NTW>(a.slab + (pg << lp) + (voff & pmask));
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int jj = 0; jj < ROWS; ++jj)
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        float s = acc[jj][i];
+        s = dot2<DT>(wq[h][jj].x, xq[h][i].x, s);
+        s = dot2<DT>(wq[h][jj].y, xq[h][i].y, s);
+        s = dot2<DT>(wq[h][jj].z, xq[h][i].z, s);
+        s = dot2<DT>(wq[h][jj].w, xq[h][i].w, s);
+        acc[jj][i] = s;
+      }
+}
+
 template <int DT, int NT, int ROWS, bool NTW, bool COH>
 __device__ __forceinline__ void shrink_valu_body(const LaunchArgs& a, const ItemRec it, const SlotRec sl,
                                                  const uint8_t* __restrict__ x, float* __restrict__ v,
@@ -1533,7 +1571,7 @@ __global__ __launch_bounds__(256, kWgPerCu) void k_expand_panel(const LaunchArgs
 // rows (expand) and add their partial sums through LDS in wavefront order, so the result does not
 // depend on timing.
 // ------------------------------------------------------------------------------------------
-template <int DT, int NT, bool NTW, bool COH = false>
+template <int DT, int NT, bool NTW, bool COH = false, bool TWO = false>
 __device__ __forceinline__ void shrink_coop_body(const LaunchArgs& a, const ItemRec it, const SlotRec sl,
                                                  const uint8_t* __restrict__ x, float* __restrict__ v,
                                                  int32_t* lds_pt, float (*red)[kShrinkRows * kValuTok]) {
@@ -1574,7 +1612,13 @@ __device__ __forceinline__ void shrink_coop_body(const LaunchArgs& a, const Item
     for (int i = 0; i < NT; ++i) acc[jj][i] = 0.f;
   constexpr int CH = kWave * VEC;
   const int full = d_in / CH * CH;
-  for (int k0 = wave * CH; k0 < full; k0 += 4 * CH)
+  int k0 = wave * CH;
+  if constexpr (TWO && NT <= 2) {
+    // two chunks' loads under way at a time: at d_in 4096 that is all a wavefront has, one trip to memory instead of two
+    for (; k0 + 4 * CH < full; k0 += 8 * CH)
+      shrink_valu_chunk2<DT, NT, kShrinkRows, NTW>(a, x, tok, lds_pt, win0, base, rowb, nrows, d_in, k0, k0 + 4 * CH, acc);
+  }
+  for (; k0 < full; k0 += 4 * CH)
     shrink_valu_chunk<DT, NT, kShrinkRows, false, NTW>(a, x, tok, lds_pt, win0, base, rowb, nrows, d_in, k0, acc);
   if (full < d_in && ((full / CH) & 3) == wave)
     shrink_valu_chunk<DT, NT, kShrinkRows, true, NTW>(a, x, tok, lds_pt, win0, base, rowb, nrows, d_in, full, acc);
@@ -1592,7 +1636,10 @@ __device__ __forceinline__ void shrink_coop_body(const LaunchArgs& a, const Item
   }
 }
 
-template <int DT>
+// TWO: items of one or two tokens keep two chunks in flight.  For launches that leave a CU one workgroup at most (4 tokens
+// through 32 layers in calls of 3 and 1 slots, 7 - 21 workgroups: 693 -> 613 us a step); larger ones lose more by the
+// registers (four instead of five workgroups fit a CU: 101 tokens, 532 workgroups, 649 against 653).
+template <int DT, bool TWO>
 __global__ __launch_bounds__(256) void k_shrink_coop(const LaunchArgs a, const SlotPtrs p) {
   __shared__ int32_t lds_pt[kPtWindow / 4];
   __shared__ float red[4][kShrinkRows * kValuTok];
@@ -1603,13 +1650,13 @@ __global__ __launch_bounds__(256) void k_shrink_coop(const LaunchArgs a, const S
   const uint8_t* x = (const uint8_t*)p.a[q];
   float* v = (float*)p.b[q];
   if (item_once(it)) {
-    if (it.ntok <= 1) shrink_coop_body<DT, 1, true>(a, it, sl, x, v, lds_pt, red);
-    else if (it.ntok == 2) shrink_coop_body<DT, 2, true>(a, it, sl, x, v, lds_pt, red);
-    else shrink_coop_body<DT, kValuTok, true>(a, it, sl, x, v, lds_pt, red);
+    if (it.ntok <= 1) shrink_coop_body<DT, 1, true, false, TWO>(a, it, sl, x, v, lds_pt, red);
+    else if (it.ntok == 2) shrink_coop_body<DT, 2, true, false, TWO>(a, it, sl, x, v, lds_pt, red);
+    else shrink_coop_body<DT, kValuTok, true, false, TWO>(a, it, sl, x, v, lds_pt, red);
   } else {
-    if (it.ntok <= 1) shrink_coop_body<DT, 1, false>(a, it, sl, x, v, lds_pt, red);
-    else if (it.ntok == 2) shrink_coop_body<DT, 2, false>(a, it, sl, x, v, lds_pt, red);
-    else shrink_coop_body<DT, kValuTok, false>(a, it, sl, x, v, lds_pt, red);
+    if (it.ntok <= 1) shrink_coop_body<DT, 1, false, false, TWO>(a, it, sl, x, v, lds_pt, red);
+    else if (it.ntok == 2) shrink_coop_body<DT, 2, false, false, TWO>(a, it, sl, x, v, lds_pt, red);
+    else shrink_coop_body<DT, kValuTok, false, false, TWO>(a, it, sl, x, v, lds_pt, red);
   }
 }
 
@@ -1967,7 +2014,7 @@ hipError_t launch_shrink(int dtype, const LaunchArgs& a0, const SlotPtrs& p, int
   if (!single && a0.n_items % 4) return hipErrorInvalidValue;  // blocks of 4 records
   // kModeDeep: as kModeBlocks with two runs in flight per matrix-core item; kModeLight: no such items in the list
   static const KernelFn table[5][3] = {{k_shrink<0, 1>, k_shrink<1, 1>, k_shrink<2, 1>},
-                                       {k_shrink_coop<0>, k_shrink_coop<1>, k_shrink_coop<2>},
+                                       {k_shrink_coop<0, false>, k_shrink_coop<1, false>, k_shrink_coop<2, false>},
                                        {k_shrink<0, 2>, k_shrink<1, 2>, k_shrink<2, 2>},
                                        {k_shrink_panel<0>, k_shrink_panel<1>, nullptr},
                                        {nullptr, nullptr, k_shrink<2, 0>}};
@@ -1982,7 +2029,9 @@ hipError_t launch_shrink(int dtype, const LaunchArgs& a0, const SlotPtrs& p, int
     a.n_items = per * nb;
     const dim3 grid = mode == kModeShrinkPanel ? dim3((nb + kXcds - 1) / kXcds * kXcds * n_slots)
                     : a.slot_fastest ? dim3(n_slots, 1, nb) : dim3(nb, 1, n_slots);
-    launch(table[mode][dtype], grid, dim3(256), st, first == 0 ? e0 : nullptr, first + step >= n_blocks ? e1 : nullptr, a, p);
+    static const KernelFn two[2] = {k_shrink_coop<0, true>, k_shrink_coop<1, true>};
+    const KernelFn k = single && dtype != 2 && (int64_t)nb * n_slots <= 256 ? two[dtype] : table[mode][dtype];
+    launch(k, grid, dim3(256), st, first == 0 ? e0 : nullptr, first + step >= n_blocks ? e1 : nullptr, a, p);
   }
   return hipGetLastError();
 }
