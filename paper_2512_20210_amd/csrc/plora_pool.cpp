@@ -224,10 +224,11 @@ constexpr int kF32MinTokens = 16;
 // tokens in calls of 3 + 1 slots, about 40 items: 346 against 327 us on average and 275 against 363 at worst; 2,048
 // tokens of prefill 2048 -> 2048, 64 items or more: 107 against 36).
 constexpr int64_t kF32MinItems = 64;
-// Batch images up to this size go by a kernel.  One projection of 16 tokens takes 24 us a step that way and 51 with the
-// side stream; steps with images near the limit measure alike (a prefill of 5,120 tokens 131 and 131 us, 161 and 183
-// when the step starts on an idle GPU), and above it the copy behind running kernels is as good.
-constexpr size_t kImageByKernel = (size_t)256 << 10;
+// Batch images up to this size go by a kernel.  One projection of 16 tokens takes 21 us a step that way and 43 with the
+// side stream, a prefill of 5,120 tokens 131 either way, and 161 against 183 when the step starts on an idle GPU.  A
+// larger image is better copied behind running kernels (1,024 tokens over 1,000 adapters, about 256 KiB: 722
+// against 718 us).
+constexpr size_t kImageByKernel = (size_t)128 << 10;
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Records the marker on its stream if that has not happened yet.
