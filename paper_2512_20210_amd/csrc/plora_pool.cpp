@@ -1082,13 +1082,19 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     // workgroup, longest chains first.  Not needed when even one slot's ordinary launch is past its limit.
     lists[op][2].clear();
     const int64_t min_grid = op == 1 ? p->min_chunks : 1;  // workgroups per block of the list in the smallest launch
-    if (!(op == 0 ? b->panel_shrink : b->panel) && p->coop_max_workgroups[op] > 0 &&
-        (int64_t)(lists[op][0].size() / 4) * min_grid <= p->coop_max_workgroups[op]) {
+    // (an expand panel batch: the groups that do not go to the panel kernel)
+    const bool light_only = op == 1 && b->panel;
+    const int64_t blocks = (int64_t)((lists[op][0].size() - (light_only ? b->n_heavy[1] : 0)) / 4);
+    if (!(op == 0 && b->panel_shrink) && p->coop_max_workgroups[op] > 0 && blocks * min_grid <= p->coop_max_workgroups[op]) {
       std::vector<ItemRec>& all = wl[op][1].items;  // reused as scratch: the matrix-core records are arranged already
       all.clear();
       size_t pt_run = 0;
       for (int32_t u = 0; u < n_seg; ++u) {
         const Adapter& a = p->ad[touched[u]];
+        if (light_only && expand_on_matrix_cores(a, p->count[touched[u]])) {
+          if (!a.contig) pt_run += a.pt.size();
+          continue;
+        }
         token_groups((int16_t)a.rank, a.scale, a.contig ? a.pt[0] : (int32_t)pt_run, (int16_t)(a.contig ? kItemContig : 0),
                      b->seg_start[u], p->count[touched[u]]);
         if (!a.contig) pt_run += a.pt.size();
@@ -1288,9 +1294,15 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     const int panel_mode = panel && 2 * chunks <= 65535 &&
                                    (int64_t)nq * (b->n_heavy[op] / 4) * chunks <= p->panel_half_max_workgroups
                                ? kModePanelHalf : kModePanel;
+    // what a panel batch has besides (decode tokens in a batch with prefill) is as often too little to fill the GPU: the
+    // cooperative kernel under the same limit (900 prefill and 93 decode tokens, ranks up to 100, calls of 3 and 1 slots
+    // 2056 -> 520 .. 2056: expand 217 -> 157 us a step; 3,000 and 64 tokens of a 7B-shaped layer 136 -> 119)
+    const bool light_coop = panel && n_all > b->n_heavy[op] && p->coop_max_workgroups[1] > 0 && b->n_items[1][2] > 0 &&
+                            (int64_t)nq * ((n_all - b->n_heavy[op]) / 4) * chunks <= p->coop_max_workgroups[1];
     const Part parts[2] = {{list, panel ? b->n_heavy[op] : n_all, panel ? panel_mode : coop ? kModeCoop : is_shrink && b->panel_shrink ? kModeShrinkPanel : deep ? kModeDeep
                            : is_shrink && p->dtype == PLORA_F32 && b->n_heavy[0] == 0 ? kModeLight : kModeBlocks},
-                           {list + b->n_heavy[op], panel ? n_all - b->n_heavy[op] : 0, kModeBlocks}};
+                           light_coop ? Part{(const ItemRec*)(b->d_img + b->off_items[1][2]), b->n_items[1][2], kModeCoop}
+                                      : Part{list + b->n_heavy[op], panel ? n_all - b->n_heavy[op] : 0, kModeBlocks}};
     plora_pool::ProfRec rec{op, nullptr, nullptr};
     if (p->profiling) {
       for (hipEvent_t* ev : {&rec.e0, &rec.e1}) {
