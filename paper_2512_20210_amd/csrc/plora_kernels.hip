@@ -13,18 +13,22 @@
 //                             of all their sums.
 //   shrink, matrix-core item: 32 rows of A x up to 32 tokens, v_mfma_f32_16x16x32 (bf16 / f16), by
 //                             4 wavefronts that split d_in; operands staged in LDS, one or two
-//                             runs of 64 k-values in flight per wavefront (two kernels).
+//                             runs of 128 bytes of a row in flight per wavefront (two kernels); fp32:
+//                             v_mfma_f32_16x16x4, in batches with many such items.
+//   shrink, panel item      : 64 rows of A x up to 64 tokens of a prefill batch, the tile shared by the
+//                             4 wavefronts and loaded straight to LDS (kernel k_shrink_panel).
 //   expand, vector-ALU item : all rows of B x 64 lanes x 16 bytes of columns x up to 4 tokens;
 //                             no reduction, read-modify-write of y.
 //   expand, matrix-core item: all rows of B x 512 columns; up to 16 tokens: every wavefront its own
 //                             128 columns, B transposed in registers; 17 to 64 tokens (only in
 //                             batches with many large groups, kernel k_expand_panel): B stationary
 //                             in LDS, one 16-token tile per wavefront.  v is split into a high and a
-//                             low half so that fp32 v loses nothing that matters.
+//                             low half so that fp32 v loses nothing that matters (fp32 pools need
+//                             neither the transposition nor the halves).
 //
 // One more launch form uses the vector-ALU records alone: the cooperative kernels for calls too small
 // to fill the machine (one record per 256-thread workgroup whose wavefronts split the record's chain
-// of loads).  k_scatter_pages moves a blob that
+// of loads).  k_copy_image fetches a batch's work lists from host memory, k_scatter_pages moves a blob that
 // arrived contiguous in a staging buffer into its pages (staged loads).
 //
 // Uniform values stay scalar: grid coordinates, slot record, work record (one 32-byte scalar load)
