@@ -100,6 +100,7 @@ struct plora_batch {
   int32_t n_heavy[2] = {0, 0};  // layout 0 only: records of the leading matrix-core blocks
   std::vector<int32_t> adapters;      // pinned adapters
   std::shared_ptr<Event> done;        // recorded by plora_batch_end; the images are reusable once it has passed
+  bool lost = false;                  // nothing says when its image is free again: not used until the pool is destroyed
   hipEvent_t ev_img = nullptr;        // the image has arrived on the device (recorded on the pool's aux stream)
   // Streams other than `stream` that kernels of this batch were launched on (the caller orders them after
   // `stream`); plora_batch_end makes `stream` wait for each of them, so that the batch's completion marker on
@@ -863,6 +864,43 @@ int plora_pool_set_option(plora_pool* p, const char* key, int64_t value) {
 // ---------------------------------------------------------------------------------------------
 // batch translation
 // ---------------------------------------------------------------------------------------------
+// Queues the transfer of a batch's image and the batch stream's waits for adapters that are still loading.  If that fails,
+// what was queued so far may still read the page-locked image and write the device's: the object then gets a
+// marker behind it, as at the end of a batch.
+static int send_image(plora_pool* p, plora_batch* b, size_t need, bool fresh_queue, const std::vector<int32_t>& touched) {
+  // A small image goes by a kernel on the batch's own stream; a large one on the pool's side stream, where it
+  // overlaps kernels already queued on `stream` (so does the first of a batch object, behind its cleared queue
+  // state, and that of a stream under capture, which has to stay out of the graph).
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool by_kernel = launch_copy_image && need <= kImageByKernel && !fresh_queue &&
+                         hipStreamIsCapturing(b->stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+  auto queue_all = [&]() -> int {
+    if (by_kernel) {
+      HIP_TRY(launch_copy_image(b->hd_img, b->d_img, need, b->stream));
+    } else {
+      (void)hipGetLastError();
+      if (!b->ev_img) HIP_TRY(hipEventCreateWithFlags(&b->ev_img, hipEventDisableTiming));
+      HIP_TRY(hipMemcpyAsync(b->d_img, b->h_img, need, hipMemcpyHostToDevice, p->aux));
+      HIP_TRY(hipEventRecord(b->ev_img, p->aux));
+      HIP_TRY(hipStreamWaitEvent(b->stream, b->ev_img, 0));
+    }
+    for (int32_t i : touched) {
+      Adapter& a = p->ad[i];
+      if (a.copy_pending && poll_ready(p, a) == 0) HIP_TRY(hipStreamWaitEvent(b->stream, a.ev_ready, 0));
+    }
+    return PLORA_OK;
+  };
+  const int rc = queue_all();
+  if (rc != PLORA_OK) {
+    const int cause = g_last_hip;
+    auto marker = std::make_shared<Event>();
+    marker->stream = by_kernel ? b->stream : p->aux;
+    if (record_now(*marker) == PLORA_OK) b->done = std::move(marker); else b->lost = true;
+    g_last_hip = cause;
+  }
+  return rc;
+}
+
 int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream s, plora_batch** out) {
   if (!p || !out || T < 0 || (T > 0 && !t2a)) return PLORA_ERR_INVAL;
   // pass 1: validate and count (nothing is modified on failure except the scratch counters)
@@ -887,7 +925,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
   plora_batch* b = nullptr;
   bool unrecorded = false;
   for (plora_batch* c : p->batches) {
-    if (c->open) continue;
+    if (c->open || c->lost) continue;
     if (c->done) {  // its last copy and kernels may still be in flight
       if (!c->done->recorded) { unrecorded = true; continue; }
       if (marker_passed(*c->done) != 1) continue;
@@ -1159,25 +1197,8 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
   b->perm.resize(n_perm);
 
   if (!p->placement_only) {
-    // A small image goes by a kernel on the batch's own stream; a large one on the pool's side stream, where it
-    // overlaps kernels already queued on `stream` (so does the first of a batch object, behind its cleared queue
-    // state, and that of a stream under capture, which has to stay out of the graph).
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const bool by_kernel = launch_copy_image && need <= kImageByKernel && !fresh_queue &&
-                           hipStreamIsCapturing(b->stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
-    if (by_kernel) {
-      HIP_TRY(launch_copy_image(b->hd_img, b->d_img, need, b->stream));
-    } else {
-      (void)hipGetLastError();
-      if (!b->ev_img) HIP_TRY(hipEventCreateWithFlags(&b->ev_img, hipEventDisableTiming));
-      HIP_TRY(hipMemcpyAsync(b->d_img, b->h_img, need, hipMemcpyHostToDevice, p->aux));
-      HIP_TRY(hipEventRecord(b->ev_img, p->aux));
-      HIP_TRY(hipStreamWaitEvent(b->stream, b->ev_img, 0));
-    }
-    for (int32_t i : touched) {
-      Adapter& a = p->ad[i];
-      if (a.copy_pending && poll_ready(p, a) == 0) HIP_TRY(hipStreamWaitEvent(b->stream, a.ev_ready, 0));
-    }
+    const int sent = send_image(p, b, need, fresh_queue, touched);
+    if (sent != PLORA_OK) return sent;
   }
   b->adapters.assign(touched.begin(), touched.end());
   for (int32_t i : touched) p->ad[i].pins++;

@@ -36,6 +36,9 @@ std::vector<ihipEvent_t*> g_dead_events;  // kept: queued operations may still n
 std::map<void*, size_t> g_host, g_dev;
 bool g_ignore_waits = false;
 int g_copy_fault_in = 0;  // > 0: that many hipMemcpyAsync calls from now, one fails
+int g_wait_fault_in = 0, g_memset_fault_in = 0;  // the same for hipStreamWaitEvent and hipMemsetAsync
+hipError_t g_last_error = hipSuccess;
+std::vector<ihipStream_t*> g_capturing;
 
 ihipStream_t* S(hipStream_t st) { return st ? st : &g_null_stream; }
 
@@ -113,6 +116,13 @@ void drain() {
 
 void set_ignore_waits(bool on) { g_ignore_waits = on; }
 void fail_copy_in(int calls) { g_copy_fault_in = calls; }
+void fail_wait_in(int calls) { g_wait_fault_in = calls; }
+void fail_memset_in(int calls) { g_memset_fault_in = calls; }
+void set_last_error(hipError_t e) { g_last_error = e; }
+void set_capturing(hipStream_t st, bool on) {
+  g_capturing.erase(std::remove(g_capturing.begin(), g_capturing.end(), S(st)), g_capturing.end());
+  if (on) g_capturing.push_back(S(st));
+}
 
 size_t pending_ops() {
   size_t n = 0;
@@ -124,7 +134,7 @@ size_t pending_ops() {
 extern "C" {
 
 hipError_t hipDeviceSynchronize(void) { fakehip::drain(); return hipSuccess; }
-hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetLastError(void) { const hipError_t e = g_last_error; g_last_error = hipSuccess; return e; }
 
 hipError_t hipStreamCreateWithFlags(hipStream_t* stream, unsigned int) {
   *stream = new ihipStream_t;
@@ -159,6 +169,7 @@ hipError_t hipStreamDestroy(hipStream_t stream) {
 
 hipError_t hipStreamWaitEvent(hipStream_t stream, hipEvent_t event, unsigned int) {
   if (!event) return hipErrorInvalidHandle;
+  if (g_wait_fault_in > 0 && --g_wait_fault_in == 0) return g_last_error = hipErrorUnknown;  // injected fault: nothing is queued
   if (event->recorded == 0) return hipSuccess;  // never recorded: nothing to wait for
   Op op;
   op.kind = Op::WAIT;
@@ -235,12 +246,14 @@ hipError_t hipHostMalloc(void** ptr, size_t size, unsigned int) {
   return hipSuccess;
 }
 
-hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* status) {
-  *status = hipStreamCaptureStatusNone;
+hipError_t hipStreamIsCapturing(hipStream_t stream, hipStreamCaptureStatus* status) {
+  const bool on = std::find(g_capturing.begin(), g_capturing.end(), S(stream)) != g_capturing.end();
+  *status = on ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
   return hipSuccess;
 }
 
 hipError_t hipMemsetAsync(void* dst, int value, size_t n, hipStream_t stream) {
+  if (g_memset_fault_in > 0 && --g_memset_fault_in == 0) return g_last_error = hipErrorUnknown;
   Op op;
   op.kind = Op::KERNEL;
   op.fn = [=] { std::memset(dst, value, n); };

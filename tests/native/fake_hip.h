@@ -26,5 +26,12 @@ void drain();
 void set_ignore_waits(bool on);
 // The `calls`-th hipMemcpyAsync from now fails (hipErrorUnknown) without queueing anything; 0 = none.
 void fail_copy_in(int calls);
+// The same for hipStreamWaitEvent and hipMemsetAsync.
+void fail_wait_in(int calls);
+void fail_memset_in(int calls);
+// What hipGetLastError returns (and clears) next: an error that the caller of the library has not looked at yet.
+void set_last_error(hipError_t e);
+// hipStreamIsCapturing reports a capture on st.
+void set_capturing(hipStream_t st, bool on);
 size_t pending_ops();
 }  // namespace fakehip

@@ -1,0 +1,130 @@
+// What plora_batch_begin leaves behind when a HIP call of it fails, and how a batch's image travels, on the CPU against
+// the stand-in HIP runtime (fake_hip.*).  One check per name given on the command line.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <memory>
+#include <string>
+#include <vector>
+
+#include "fake_hip.h"
+#include "plora.h"
+#include "plora_internal.h"
+
+#define CHECK(c) do { if (!(c)) { std::printf("CHECK failed at line %d: %s\n", __LINE__, #c); std::exit(1); } } while (0)
+
+namespace {
+int g_image_launches = 0;             // images sent by a kernel
+int g_image_fault_in = 0;             // > 0: that many launches from now, one is queued and reports an error all the same
+int g_image_checks = 0;               // image kernels that have run
+hipStream_t g_image_stream = nullptr; // stream of the last one
+long g_fused_runs = 0;
+}  // namespace
+
+namespace plora {
+hipError_t launch_shrink(int, const LaunchArgs&, const SlotPtrs&, int, int, hipStream_t, hipEvent_t, hipEvent_t) { return hipSuccess; }
+hipError_t launch_expand(int, const LaunchArgs&, const SlotPtrs&, int, int, int, hipStream_t, hipEvent_t, hipEvent_t) { return hipSuccess; }
+hipError_t launch_scatter(const uint8_t*, uint8_t*, int, uint64_t, const int32_t*, uint32_t, hipStream_t) { return hipSuccess; }
+// When the stream reaches it, the page-locked image has to be what it was when the kernel was queued.
+hipError_t launch_copy_image(const void* src, void* dst, size_t bytes, hipStream_t st) {
+  auto then = std::make_shared<std::vector<uint8_t>>((const uint8_t*)src, (const uint8_t*)src + bytes);
+  fakehip::enqueue_kernel(st, [=] {
+    CHECK(std::memcmp(src, then->data(), bytes) == 0);
+    std::memcpy(dst, src, bytes);
+    ++g_image_checks;
+  });
+  ++g_image_launches;
+  g_image_stream = st;
+  if (g_image_fault_in > 0 && --g_image_fault_in == 0) return hipErrorUnknown;
+  return hipSuccess;
+}
+// The one-launch form's counters have to be clear when a batch object's first launch runs.
+hipError_t launch_delta_queue(int, const FusedArgs& f, const FusedPtrs&, hipStream_t st, hipEvent_t, hipEvent_t) {
+  const uint32_t* queue = f.queue;
+  fakehip::enqueue_kernel(st, [=] {
+    for (int i = 0; i < kQueueWords; ++i) CHECK(queue[i] == 0);
+    ++g_fused_runs;
+  });
+  return hipSuccess;
+}
+uint64_t static_scratch_bytes() { return 0; }
+hipError_t static_scratch(void**) { return hipErrorNotSupported; }
+}  // namespace plora
+
+namespace {
+struct Fixture {
+  plora_pool* p = nullptr;
+  hipStream_t st = nullptr, other = nullptr, copy = nullptr;
+  void *blob = nullptr, *x = nullptr, *v = nullptr, *y = nullptr;
+  Fixture() {
+    const int32_t d_in[1] = {64}, d_out[1] = {32};
+    plora_layout lay{1, d_in, d_out, PLORA_BF16, 4, 16};
+    CHECK(plora_pool_create(4096, 16, &lay, nullptr, 0, &p) == PLORA_OK);
+    for (auto* s : {&st, &other, &copy}) CHECK(hipStreamCreateWithFlags(s, hipStreamNonBlocking) == hipSuccess);
+    CHECK(hipHostMalloc(&blob, plora_adapter_bytes(p, 16), 0) == hipSuccess);
+    for (void** q : {&x, &v, &y}) CHECK(hipMalloc(q, 1 << 16) == hipSuccess);
+    for (int i = 0; i < 3; ++i) CHECK(plora_load_adapter(p, i, 16, 1.f, blob, copy, nullptr, nullptr) == PLORA_OK);
+    fakehip::drain();
+  }
+  ~Fixture() {
+    CHECK(plora_pool_destroy(p) == PLORA_OK);
+    CHECK(hipHostFree(blob) == hipSuccess);
+    for (void* q : {x, v, y}) CHECK(hipFree(q) == hipSuccess);
+    for (hipStream_t s : {st, other, copy}) CHECK(hipStreamDestroy(s) == hipSuccess);
+  }
+  // one batch of n tokens of adapter a on stream s, begun and ended (nothing runs); the begin's result
+  int batch(int a, int n, hipStream_t s) {
+    std::vector<int32_t> t2a(n, a);
+    plora_batch* b = nullptr;
+    const int rc = plora_batch_begin(p, t2a.data(), n, s, &b);
+    if (rc == PLORA_OK) CHECK(plora_batch_end(p, b) == PLORA_OK);
+    return rc;
+  }
+  void recycled() {  // a batch object whose first image has passed
+    CHECK(plora_pool_set_option(p, "batches_per_marker", 1) == PLORA_OK);
+    CHECK(batch(0, 8, st) == PLORA_OK);
+    fakehip::drain();
+    g_image_launches = g_image_checks = 0;
+  }
+};
+
+// A begin that fails after its image was queued must not hand the image's buffers to the next batch.
+void image_in_flight() {
+  for (int how = 0; how < 3; ++how) {
+    Fixture f;
+    f.recycled();
+    if (how == 0) g_image_fault_in = 1;  // the launch itself is reported as failed
+    if (how == 1) {                      // the wait for an adapter that is still loading fails
+      CHECK(plora_load_adapter(f.p, 3, 16, 1.f, f.blob, f.copy, nullptr, nullptr) == PLORA_OK);
+      fakehip::fail_wait_in(1);
+    }
+    if (how < 2) CHECK(f.batch(how == 1 ? 3 : 1, 8, f.st) == PLORA_ERR_HIP);
+    if (how == 2) {  // an image for the side stream (the first of a second object), and the wait for it fails
+      int32_t t2a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+      plora_batch* open = nullptr;
+      CHECK(plora_batch_begin(f.p, t2a, 8, f.st, &open) == PLORA_OK);  // holds the recycled object
+      fakehip::fail_wait_in(1);
+      CHECK(f.batch(1, 8, f.st) == PLORA_ERR_HIP);
+      CHECK(plora_batch_end(f.p, open) == PLORA_OK);
+    }
+    g_image_fault_in = 0;
+    fakehip::fail_wait_in(0);
+    // more batches, also with larger images and on another stream, while the first image still waits
+    for (int k = 0; k < 4; ++k) CHECK(f.batch(2, 5 + 400 * k, k % 2 ? f.other : f.st) == PLORA_OK);
+    fakehip::drain();
+    CHECK(g_image_checks == g_image_launches && (how == 2 || g_image_launches >= 1));
+    CHECK(f.batch(2, 16, f.st) == PLORA_OK);  // and the objects come back into use
+    fakehip::drain();
+  }
+}
+}  // namespace
+
+int main(int argc, char** argv) {
+  for (int i = 1; i < argc; ++i) {
+    const std::string name = argv[i];
+    if (name == "image_in_flight") image_in_flight();
+    else return 2;
+    std::printf("%s OK\n", name.c_str());
+  }
+  return 0;
+}
