@@ -871,14 +871,17 @@ static int send_image(plora_pool* p, plora_batch* b, size_t need, bool fresh_que
   // A small image goes by a kernel on the batch's own stream; a large one on the pool's side stream, where it
   // overlaps kernels already queued on `stream` (so does the first of a batch object, behind its cleared queue
   // state, and that of a stream under capture, which has to stay out of the graph).
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  const bool by_kernel = launch_copy_image && need <= kImageByKernel && !fresh_queue &&
-                         hipStreamIsCapturing(b->stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+  bool by_kernel = launch_copy_image && need <= kImageByKernel && !fresh_queue;
+  if (by_kernel) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(b->stream, &capture);
+    if (e != hipSuccess) (void)hipGetLastError();  // (its own error; one of the caller's stays where it is)
+    by_kernel = e == hipSuccess && capture == hipStreamCaptureStatusNone;
+  }
   auto queue_all = [&]() -> int {
     if (by_kernel) {
       HIP_TRY(launch_copy_image(b->hd_img, b->d_img, need, b->stream));
     } else {
-      (void)hipGetLastError();
       if (!b->ev_img) HIP_TRY(hipEventCreateWithFlags(&b->ev_img, hipEventDisableTiming));
       HIP_TRY(hipMemcpyAsync(b->d_img, b->h_img, need, hipMemcpyHostToDevice, p->aux));
       HIP_TRY(hipEventRecord(b->ev_img, p->aux));

@@ -117,12 +117,30 @@ void image_in_flight() {
     fakehip::drain();
   }
 }
+
+// An error that the caller has not looked at is still there after a begin, whichever way the image goes.
+void callers_error() {
+  Fixture f;
+  CHECK(plora_pool_set_option(f.p, "batches_per_marker", 1) == PLORA_OK);
+  struct { int n; bool capturing; int kernels; } way[] = {{8, false, 0}, {8, false, 1}, {60000, false, 0}, {8, true, 0}};
+  for (auto& w : way) {  // the first of an object, a small one by kernel, one over the limit, one on a stream under capture
+    fakehip::set_capturing(f.st, w.capturing);
+    g_image_launches = 0;
+    fakehip::set_last_error(hipErrorInvalidDevice);
+    CHECK(f.batch(0, w.n, f.st) == PLORA_OK);
+    CHECK(hipGetLastError() == hipErrorInvalidDevice);
+    CHECK(g_image_launches == w.kernels);
+    fakehip::set_capturing(f.st, false);
+    fakehip::drain();
+  }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
   for (int i = 1; i < argc; ++i) {
     const std::string name = argv[i];
     if (name == "image_in_flight") image_in_flight();
+    else if (name == "callers_error") callers_error();
     else return 2;
     std::printf("%s OK\n", name.c_str());
   }
