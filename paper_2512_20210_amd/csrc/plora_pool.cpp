@@ -90,6 +90,7 @@ struct plora_batch {
   // state of the one-launch form of plora_delta: counters and flags on the device (zero when allocated,
   // never reset), and the value each slot position's counter will have reached after the launches so far
   uint32_t* d_queue = nullptr;
+  bool queue_cleared = false;  // cleared on the pool's side stream, and an image has gone behind that
   mutable uint32_t q_target[kMaxSlotsFused] = {};
   // work lists (blocks of 4 records): [op][layout], op 0 = shrink, 1 = expand; layout 0 = longest
   // first (for launches whose fastest grid dimension is the slot), 1 = dealt into 8 interleaved XCD
@@ -867,11 +868,11 @@ int plora_pool_set_option(plora_pool* p, const char* key, int64_t value) {
 // Queues the transfer of a batch's image and the batch stream's waits for adapters that are still loading.  If that fails,
 // what was queued so far may still read the page-locked image and write the device's: the object then gets a
 // marker behind it, as at the end of a batch.
-static int send_image(plora_pool* p, plora_batch* b, size_t need, bool fresh_queue, const std::vector<int32_t>& touched) {
+static int send_image(plora_pool* p, plora_batch* b, size_t need, const std::vector<int32_t>& touched) {
   // A small image goes by a kernel on the batch's own stream; a large one on the pool's side stream, where it
-  // overlaps kernels already queued on `stream` (so does the first of a batch object, behind its cleared queue
-  // state, and that of a stream under capture, which has to stay out of the graph).
-  bool by_kernel = launch_copy_image && need <= kImageByKernel && !fresh_queue;
+  // overlaps kernels already queued on `stream` (so does the first of a batch object, behind the clearing of
+  // its counters, and that of a stream under capture, which has to stay out of the graph).
+  bool by_kernel = launch_copy_image && need <= kImageByKernel && b->queue_cleared;
   if (by_kernel) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     const hipError_t e = hipStreamIsCapturing(b->stream, &capture);
@@ -883,9 +884,11 @@ static int send_image(plora_pool* p, plora_batch* b, size_t need, bool fresh_que
       HIP_TRY(launch_copy_image(b->hd_img, b->d_img, need, b->stream));
     } else {
       if (!b->ev_img) HIP_TRY(hipEventCreateWithFlags(&b->ev_img, hipEventDisableTiming));
+      if (!b->queue_cleared) HIP_TRY(hipMemsetAsync(b->d_queue, 0, kQueueWords * sizeof(uint32_t), p->aux));
       HIP_TRY(hipMemcpyAsync(b->d_img, b->h_img, need, hipMemcpyHostToDevice, p->aux));
       HIP_TRY(hipEventRecord(b->ev_img, p->aux));
       HIP_TRY(hipStreamWaitEvent(b->stream, b->ev_img, 0));
+      b->queue_cleared = true;
     }
     for (int32_t i : touched) {
       Adapter& a = p->ad[i];
@@ -1160,7 +1163,6 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
       off = align_up(off + lists[op][k].size() * sizeof(ItemRec), 256);
     }
   const size_t need = std::max<size_t>(off, 256);
-  bool fresh_queue = false;  // cleared on the side stream: this batch's image has to travel there as well
   if (need > b->cap) {
     const size_t cap = align_up(need + need / 2, 4096);
     if (p->placement_only) {
@@ -1174,11 +1176,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
       HIP_TRY(hipHostMalloc((void**)&b->h_img, cap, hipHostMallocDefault));
       HIP_TRY(hipHostGetDevicePointer((void**)&b->hd_img, b->h_img, 0));
       HIP_TRY(hipMalloc((void**)&b->d_img, cap));
-      if (!b->d_queue) {
-        fresh_queue = true;
-        HIP_TRY(hipMalloc((void**)&b->d_queue, kQueueWords * sizeof(uint32_t)));
-        HIP_TRY(hipMemsetAsync(b->d_queue, 0, kQueueWords * sizeof(uint32_t), p->aux));  // ahead of the image copy below
-      }
+      if (!b->d_queue) HIP_TRY(hipMalloc((void**)&b->d_queue, kQueueWords * sizeof(uint32_t)));
     }
     b->cap = cap;
   }
@@ -1200,7 +1198,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
   b->perm.resize(n_perm);
 
   if (!p->placement_only) {
-    const int sent = send_image(p, b, need, fresh_queue, touched);
+    const int sent = send_image(p, b, need, touched);
     if (sent != PLORA_OK) return sent;
   }
   b->adapters.assign(touched.begin(), touched.end());

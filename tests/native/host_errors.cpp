@@ -134,6 +134,33 @@ void callers_error() {
     fakehip::drain();
   }
 }
+
+// A batch object whose counters could not be cleared at first clears them later, and always ahead of its first launch.
+void counters_cleared() {
+  for (int how = 0; how < 2; ++how) {
+    Fixture f;
+    CHECK(plora_pool_set_option(f.p, "fused_max_tasks", 1 << 20) == PLORA_OK);
+    if (how == 0) fakehip::fail_memset_in(1);
+    if (how == 1) fakehip::fail_wait_in(1);  // the batch stream's wait for the image, behind the clearing
+    CHECK(f.batch(0, 8, f.st) == PLORA_ERR_HIP);
+    fakehip::fail_memset_in(0);
+    fakehip::fail_wait_in(0);
+    g_fused_runs = 0;
+    for (int k = 0; k < 3; ++k) {
+      std::vector<int32_t> t2a(8, k);
+      plora_batch* b = nullptr;
+      const void* x = f.x;
+      float* v = (float*)f.v;
+      void* y = f.y;
+      CHECK(plora_batch_begin(f.p, t2a.data(), 8, f.st, &b) == PLORA_OK);
+      CHECK(plora_delta(f.p, b, 0, 1, &x, &v, &y, f.st) == PLORA_OK);
+      CHECK(plora_batch_end(f.p, b) == PLORA_OK);
+      while (fakehip::step(f.st)) {}  // the batch stream as far as it gets without the others
+    }
+    fakehip::drain();
+    CHECK(g_fused_runs == 3);
+  }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -141,6 +168,7 @@ int main(int argc, char** argv) {
     const std::string name = argv[i];
     if (name == "image_in_flight") image_in_flight();
     else if (name == "callers_error") callers_error();
+    else if (name == "counters_cleared") counters_cleared();
     else return 2;
     std::printf("%s OK\n", name.c_str());
   }
