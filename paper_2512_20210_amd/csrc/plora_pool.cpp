@@ -158,7 +158,7 @@ struct plora_pool {
   // A group of n tokens on a rank-r adapter takes matrix-core items when n >= min_tokens or its work
   // reaches min_work (min_tokens 0 = never).  Shrink: work = n * r.  Expand: work = n * r * (r / r
   // rounded up to 32), the second factor being the used part of the 32-row contraction tile.
-  int mfma_min_tokens = 16, mfma_min_tokens_expand = 64;
+  int mfma_min_tokens = -1, mfma_min_tokens_expand = -1;  // -1 = not set: kMinTokens / kF32MinTokens
   int64_t mfma_min_work = 64, mfma_min_work_expand = 128;
   // launch geometry, [shrink, expand]
   int xcd_remap[2] = {1, 0};  // item-fastest launches take the lists dealt into XCD queues
@@ -218,9 +218,10 @@ int poll_ready(plora_pool* p, Adapter& a) {
   return 1;
 }
 
-// fp32 groups take matrix-core items from this many tokens on ...
-constexpr int kF32MinTokens = 16;
-// ... in shrink only if the batch has at least this many such items: an item's products alone are 28 us on its four
+// Groups take matrix-core items from this many tokens on, [shrink, expand] ...
+constexpr int kMinTokens[2] = {16, 64};
+constexpr int kF32MinTokens = 16;  // (fp32 pools, both)
+// ... in fp32 shrink only if the batch has at least this many such items: an item's products alone are 28 us on its four
 // SIMDs at d_in 4096, so a few items are a longer chain than the vector-ALU items they replace (256 tokens over 64
 // adapters, 4 slots 4096 -> 4096 a call: 36 us a launch with vector-ALU items, 43 - 50 with 8 matrix-core items; 1,024
 // tokens in calls of 3 + 1 slots, about 40 items: 346 against 327 us on average and 275 against 363 at worst; 2,048
@@ -984,11 +985,13 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     }
   };
   constexpr int kTokBlock = 128;
+  const int min_tokens_s = p->mfma_min_tokens >= 0 ? p->mfma_min_tokens : half ? kMinTokens[0] : kF32MinTokens;
+  const int min_tokens_e = p->mfma_min_tokens_expand >= 0 ? p->mfma_min_tokens_expand : half ? kMinTokens[1] : kF32MinTokens;
   auto expand_on_matrix_cores = [&](const Adapter& a, int32_t n) {
     const int64_t r32 = ((int64_t)a.rank + 31) / 32 * 32;
-    if (p->mfma_min_tokens_expand <= 0) return false;
-    if (!half) return n >= std::min(p->mfma_min_tokens_expand, kF32MinTokens);
-    return n >= p->mfma_min_tokens_expand || (int64_t)n * a.rank * a.rank >= p->mfma_min_work_expand * r32;
+    if (min_tokens_e <= 0) return false;
+    if (!half) return n >= min_tokens_e;
+    return n >= min_tokens_e || (int64_t)n * a.rank * a.rank >= p->mfma_min_work_expand * r32;
   };
   // How the large groups' expand work is cut: a batch with many 64-token blocks (prefill) keeps them
   // (B is then staged once per 64 tokens) and runs them in the panel kernel; a batch with few
@@ -1001,18 +1004,18 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
       for (int32_t left = std::min(n - b0, kTokBlock); left > p->cols_max_group; left -= kMfmaTokE) ++panel_blocks;
   }
   b->panel = half && p->panel_min_blocks > 0 && panel_blocks >= p->panel_min_blocks;
-  // fp32: matrix-core shrink items only in a batch with many of them, see kF32MinItems (an explicit threshold below the
-  // default asks for them in any batch)
-  int64_t f32_items = p->mfma_min_tokens < kF32MinTokens ? kF32MinItems : 0;
+  // fp32: matrix-core shrink items only in a batch with many of them, see kF32MinItems (a threshold that was set asks for
+  // them in any batch)
+  int64_t f32_items = p->mfma_min_tokens >= 0 ? kF32MinItems : 0;
   for (int32_t u = 0; u < n_seg && !half; ++u) {
     const int32_t n = p->count[touched[u]];
-    if (n >= kF32MinTokens)
+    if (n >= min_tokens_s)
       f32_items += (int64_t)((n + kMfmaTokS - 1) / kMfmaTokS) * ((p->ad[touched[u]].rank + kMfmaRows - 1) / kMfmaRows);
   }
   auto shrink_on_matrix_cores = [&](const Adapter& a, int32_t n) {
-    if (p->mfma_min_tokens <= 0) return false;
-    if (!half) return f32_items >= kF32MinItems && n >= std::min(p->mfma_min_tokens, kF32MinTokens);
-    return n >= p->mfma_min_tokens || (int64_t)n * a.rank >= p->mfma_min_work;
+    if (min_tokens_s <= 0) return false;
+    if (!half) return f32_items >= kF32MinItems && n >= min_tokens_s;
+    return n >= min_tokens_s || (int64_t)n * a.rank >= p->mfma_min_work;
   };
   int64_t panel_tiles = 0;
   for (int32_t u = 0; u < n_seg && p->panel_min_tiles_shrink >= 0 && p->panel_shrink_fits; ++u) {

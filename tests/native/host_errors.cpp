@@ -1,5 +1,5 @@
-// What plora_batch_begin leaves behind when a HIP call of it fails, and how a batch's image travels, on the CPU against
-// the stand-in HIP runtime (fake_hip.*).  One check per name given on the command line.
+// What plora_batch_begin leaves behind when a HIP call of it fails, how a batch's image travels and which items its lists
+// hold, on the CPU against the stand-in HIP runtime (fake_hip.*).  One check per name given on the command line.
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -19,11 +19,24 @@ int g_image_fault_in = 0;             // > 0: that many launches from now, one i
 int g_image_checks = 0;               // image kernels that have run
 hipStream_t g_image_stream = nullptr; // stream of the last one
 long g_fused_runs = 0;
+int g_items[2][3];                    // [op][kind]: records that the launches read
 }  // namespace
 
 namespace plora {
-hipError_t launch_shrink(int, const LaunchArgs&, const SlotPtrs&, int, int, hipStream_t, hipEvent_t, hipEvent_t) { return hipSuccess; }
-hipError_t launch_expand(int, const LaunchArgs&, const SlotPtrs&, int, int, int, hipStream_t, hipEvent_t, hipEvent_t) { return hipSuccess; }
+void count_items(int op, const LaunchArgs& a, hipStream_t st) {
+  fakehip::enqueue_kernel(st, [=] {
+    for (int i = 0; i < a.n_items; ++i)
+      if (a.items[i].kind >= 0) { CHECK((a.items[i].kind & 0xff) < 3); ++g_items[op][a.items[i].kind & 0xff]; }
+  });
+}
+hipError_t launch_shrink(int, const LaunchArgs& a, const SlotPtrs&, int, int, hipStream_t st, hipEvent_t, hipEvent_t) {
+  count_items(0, a, st);
+  return hipSuccess;
+}
+hipError_t launch_expand(int, const LaunchArgs& a, const SlotPtrs&, int, int, int, hipStream_t st, hipEvent_t, hipEvent_t) {
+  count_items(1, a, st);
+  return hipSuccess;
+}
 hipError_t launch_scatter(const uint8_t*, uint8_t*, int, uint64_t, const int32_t*, uint32_t, hipStream_t) { return hipSuccess; }
 // When the stream reaches it, the page-locked image has to be what it was when the kernel was queued.
 hipError_t launch_copy_image(const void* src, void* dst, size_t bytes, hipStream_t st) {
@@ -56,9 +69,9 @@ struct Fixture {
   plora_pool* p = nullptr;
   hipStream_t st = nullptr, other = nullptr, copy = nullptr;
   void *blob = nullptr, *x = nullptr, *v = nullptr, *y = nullptr;
-  Fixture() {
+  explicit Fixture(int dtype = PLORA_BF16) {
     const int32_t d_in[1] = {64}, d_out[1] = {32};
-    plora_layout lay{1, d_in, d_out, PLORA_BF16, 4, 16};
+    plora_layout lay{1, d_in, d_out, dtype, 4, 16};
     CHECK(plora_pool_create(4096, 16, &lay, nullptr, 0, &p) == PLORA_OK);
     for (auto* s : {&st, &other, &copy}) CHECK(hipStreamCreateWithFlags(s, hipStreamNonBlocking) == hipSuccess);
     CHECK(hipHostMalloc(&blob, plora_adapter_bytes(p, 16), 0) == hipSuccess);
@@ -79,6 +92,18 @@ struct Fixture {
     const int rc = plora_batch_begin(p, t2a.data(), n, s, &b);
     if (rc == PLORA_OK) CHECK(plora_batch_end(p, b) == PLORA_OK);
     return rc;
+  }
+  // the same with its delta, run to the end: g_items says what the lists held
+  void delta(const std::vector<int32_t>& t2a) {
+    plora_batch* b = nullptr;
+    const void* xs = x;
+    float* vs = (float*)v;
+    void* ys = y;
+    std::memset(g_items, 0, sizeof(g_items));
+    CHECK(plora_batch_begin(p, t2a.data(), (int32_t)t2a.size(), st, &b) == PLORA_OK);
+    CHECK(plora_delta(p, b, 0, 1, &xs, &vs, &ys, st) == PLORA_OK);
+    CHECK(plora_batch_end(p, b) == PLORA_OK);
+    fakehip::drain();
   }
   void recycled() {  // a batch object whose first image has passed
     CHECK(plora_pool_set_option(p, "batches_per_marker", 1) == PLORA_OK);
@@ -161,6 +186,26 @@ void counters_cleared() {
     CHECK(g_fused_runs == 3);
   }
 }
+
+// fp32 pools: an explicit threshold holds as it is given, for each operation by itself; unset, the library's own.
+void fp32_thresholds() {
+  struct { int shrink, expand; int64_t tokens; bool mfma_s, mfma_e; } want[] = {
+    {-1, -1, 15, false, false}, {-1, -1, 16, false, true},  // (a lone group is too little for the shrink's)
+    {1, -1, 8, true, false},    {-1, 1, 8, false, true},
+    {32, -1, 31, false, true},  {32, -1, 32, true, true},  {16, -1, 16, true, true},
+    {-1, 40, 39, false, false}, {-1, 40, 40, false, true}, {0, 0, 48, false, false},
+  };
+  for (auto& w : want) {
+    Fixture f(PLORA_F32);
+    for (const char* k : {"coop_max_workgroups_shrink", "coop_max_workgroups_expand"}) CHECK(plora_pool_set_option(f.p, k, 0) == PLORA_OK);
+    if (w.shrink >= 0) CHECK(plora_pool_set_option(f.p, "mfma_min_tokens", w.shrink) == PLORA_OK);
+    if (w.expand >= 0) CHECK(plora_pool_set_option(f.p, "mfma_min_tokens_expand", w.expand) == PLORA_OK);
+    f.delta(std::vector<int32_t>((size_t)w.tokens, 0));
+    std::printf("thresholds %d %d, %d tokens: %d and %d matrix-core items\n", w.shrink, w.expand, (int)w.tokens, g_items[0][1], g_items[1][1]);
+    CHECK((g_items[0][1] > 0) == w.mfma_s && (g_items[0][0] > 0) == !w.mfma_s);
+    CHECK((g_items[1][1] > 0) == w.mfma_e && (g_items[1][0] > 0) == !w.mfma_e);
+  }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -169,6 +214,7 @@ int main(int argc, char** argv) {
     if (name == "image_in_flight") image_in_flight();
     else if (name == "callers_error") callers_error();
     else if (name == "counters_cleared") counters_cleared();
+    else if (name == "fp32_thresholds") fp32_thresholds();
     else return 2;
     std::printf("%s OK\n", name.c_str());
   }

@@ -1,4 +1,4 @@
-"""Error paths of plora_batch_begin and the way of its image, on the CPU: tests/native/host_errors.cpp links the library's host
+"""Error paths of plora_batch_begin, the way of its image and the items of its lists, on the CPU: tests/native/host_errors.cpp links the library's host
 code against the stand-in HIP runtime of tests/native/fake_hip.cpp, whose calls can be made to fail."""
 import os
 import shutil
@@ -24,7 +24,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["image_in_flight", "callers_error", "counters_cleared"])
+@pytest.mark.parametrize("check", ["image_in_flight", "callers_error", "counters_cleared", "fp32_thresholds"])
 def test_batch_begin(exe, check):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0", UBSAN_OPTIONS="print_stacktrace=1")
     r = subprocess.run([exe, check], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120, env=env)
