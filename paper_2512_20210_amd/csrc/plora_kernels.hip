@@ -1965,11 +1965,14 @@ __global__ __launch_bounds__(256) void k_copy_image(const uint4* __restrict__ sr
 
 hipError_t launch_copy_image(const void* src, void* dst, size_t bytes, hipStream_t st) {
   if (!src || !dst || (bytes & 15) || bytes >> 32) return hipErrorInvalidValue;
-  const uint32_t n = (uint32_t)(bytes / 16);
+  const uint4* from = (const uint4*)src;
+  uint4* to = (uint4*)dst;
+  uint32_t n = (uint32_t)(bytes / 16);
   if (n == 0) return hipSuccess;
   const uint32_t wg = (n + 255) / 256;
-  hipLaunchKernelGGL(k_copy_image, dim3(wg < 64 ? wg : 64), dim3(256), 0, st, (const uint4*)src, (uint4*)dst, n);
-  return hipGetLastError();
+  void* args[3] = {&from, &to, &n};
+  // (the launch's own status: the thread's last error may be an older one of the caller's)
+  return hipLaunchKernel((const void*)k_copy_image, dim3(wg < 64 ? wg : 64), dim3(256), args, 0, st);
 }
 
 // ------------------------------------------------------------------------------------------
