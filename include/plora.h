@@ -233,7 +233,8 @@ int plora_pool_stats(plora_pool* pool, plora_stats* out);
  * whose ordinary launch would have at most this many workgroups is too small to fill the GPU and bound
  * by its longest chain of dependent loads; it runs the cooperative kernels instead, in which the four
  * wavefronts of a workgroup share one vector-ALU item; defaults 192 / 2500, 0 = never; take effect for
- * batches begun afterwards; in a batch with expand blocks of 64 tokens the limit is held against what it has besides).
+ * batches begun afterwards; in a batch with expand blocks of 64 tokens the limit is held against what it has besides,
+ * in one with shrink tiles of 64 x 64 it is at most 64, against the launch without them).
  * "batches_per_marker" (1..64, default 4: plora_batch_end puts one completion
  * event on the stream per this many batches instead of one per batch; the library records a pending
  * one itself whenever an eviction, a load or the reuse of a batch object has to order against it, so
@@ -243,9 +244,10 @@ int plora_pool_stats(plora_pool* pool, plora_stats* out);
  * many such blocks (prefill); other batches (decode: a hot adapter or two) cut them into items of 16
  * tokens for the ordinary kernel instead (0 = always).  "mfma_cols_max_group" (default 32): in a
  * batch of the first kind, a group's last <= this many tokens still go as 16-token items.
- * "panel_min_tiles_shrink" (>= -1, default 32): shrink cuts the large adapter groups of a batch into tiles of up to 64
+ * "panel_min_tiles_shrink" (>= -1, default 32): shrink can cut the large adapter groups of a batch into tiles of up to 64
  * tokens x 64 rows of A that a whole workgroup shares when the batch has at least this many of them (prefill) and
- * every d_in of the pool is a multiple of 64; otherwise into items of 32 x 32 (-1 = never, 0 = whenever there is one).
+ * every d_in of the pool is a multiple of 64; a launch of such a batch takes them when tiles x slots fill the GPU, and items
+ * of 32 x 32 otherwise, as other batches do (-1 = never; 0 = in any batch that has one, and in every launch).
  * "panel_half_max_workgroups" (>= 0, default 8192): a launch of that kernel with at most this many
  * workgroups of 512 columns is issued with one workgroup per 256 columns instead (twice as many, each
  * half as long; v is then read twice as often), which is faster while the launch is too short to hide

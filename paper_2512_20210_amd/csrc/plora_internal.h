@@ -61,7 +61,7 @@ struct LaunchArgs {
   const SlotRec* slots;   // indexed by absolute slot number
   int64_t elems_per_rank; // sum over all slots of (d_in + d_out)
   int32_t n_items;
-  int32_t pad0;
+  int32_t n_lone;         // shrink: so many blocks at the head of the list are a single record each (the others four)
   int32_t log2_page;
   int32_t v_stride;       // = max_rank
   int32_t slot_fastest;   // 1: grid = (slots, items, chunks); 0: grid = (items, chunks, slots); 2 (expand): (chunks, items, slots)

@@ -1464,7 +1464,9 @@ __global__ __launch_bounds__(256, kWgPerCu) void k_shrink(const LaunchArgs a, co
   const SlotRec sl = a.slots[p.slot[q]];
   const uint8_t* x = (const uint8_t*)p.a[q];
   float* v = (float*)p.b[q];
-  const ItemRec first = load_item(a.items + (4 * blk));
+  const bool lone = blk < a.n_lone;
+  const ItemRec* rec = a.items + (lone ? blk : 4 * blk - 3 * a.n_lone);
+  const ItemRec first = load_item(rec);
   if constexpr (DEPTH > 0) {
     if (item_kind(first) == 1) {
       if (item_once(first)) shrink_mfma4_body<DT, true, DEPTH>(a, first, sl, x, v, tile, lds_pt);
@@ -1472,8 +1474,9 @@ __global__ __launch_bounds__(256, kWgPerCu) void k_shrink(const LaunchArgs a, co
       return;
     }
   }
+  if (lone) return;  // padding
   const int wave = wave_id();
-  const ItemRec it = load_item(a.items + (4 * blk + wave));
+  const ItemRec it = load_item(rec + wave);
   if (it.kind < 0) return;  // this path has no workgroup barrier: a wavefront may leave alone
   shrink_valu_item<DT>(a, it, sl, x, v, lds_pt + wave * (kPtWindow / 4));
 }
@@ -1815,7 +1818,7 @@ __global__ __launch_bounds__(256, kWgPerCu) void k_delta_queue(const FusedArgs f
   __shared__ int s_ready;
   LaunchArgs a;
   a.slab = f.slab; a.perm = f.perm; a.pt = f.pt; a.items = nullptr; a.slots = f.slots;
-  a.elems_per_rank = f.elems_per_rank; a.n_items = 0; a.pad0 = 0; a.log2_page = f.log2_page; a.v_stride = f.v_stride;
+  a.elems_per_rank = f.elems_per_rank; a.n_items = 0; a.n_lone = 0; a.log2_page = f.log2_page; a.v_stride = f.v_stride;
   a.slot_fastest = 0; a.n_slots = 0;
   const int per_slot_e = f.n_e * f.chunks;
   const int total_s = f.n_s * f.n_slots;
@@ -2018,7 +2021,9 @@ hipError_t launch_shrink(int dtype, const LaunchArgs& a0, const SlotPtrs& p, int
                          hipEvent_t e0, hipEvent_t e1) {
   const bool single = mode == kModeCoop;  // one record per workgroup
   if (a0.n_items <= 0 || n_slots <= 0) return hipSuccess;
-  if (!single && a0.n_items % 4) return hipErrorInvalidValue;  // blocks of 4 records
+  const bool lone = !single && a0.n_lone > 0;
+  if (lone && (a0.n_lone > a0.n_items || a0.slot_fastest || mode == kModeShrinkPanel)) return hipErrorInvalidValue;
+  if (!single && (a0.n_items - a0.n_lone) % 4) return hipErrorInvalidValue;  // blocks of 4 records
   // kModeDeep: as kModeBlocks with two runs in flight per matrix-core item; kModeLight: no such items in the list
   static const KernelFn table[5][3] = {{k_shrink<0, 1>, k_shrink<1, 1>, k_shrink<2, 1>},
                                        {k_shrink_coop<0, false>, k_shrink_coop<1, false>, k_shrink_coop<2, false>},
@@ -2028,12 +2033,12 @@ hipError_t launch_shrink(int dtype, const LaunchArgs& a0, const SlotPtrs& p, int
   if (mode < 0 || mode > 4 || dtype < 0 || dtype > 2 || !table[mode][dtype]) return hipErrorInvalidValue;
   LaunchArgs a = a0;
   const int per = single ? 1 : 4;  // records per workgroup
-  const int n_blocks = a0.n_items / per;
+  const int n_blocks = (a0.n_items - a0.n_lone) / per + a0.n_lone;
   const int step = a0.slot_fastest ? 65535 : n_blocks;  // grid.z is limited to 65535
   for (int first = 0; first < n_blocks; first += step) {
     const int nb = n_blocks - first < step ? n_blocks - first : step;
     a.items = a0.items + per * first;
-    a.n_items = per * nb;
+    a.n_items = lone ? a0.n_items : per * nb;
     const dim3 grid = mode == kModeShrinkPanel ? dim3((nb + kXcds - 1) / kXcds * kXcds * n_slots)
                     : a.slot_fastest ? dim3(n_slots, 1, nb) : dim3(nb, 1, n_slots);
     static const KernelFn two[2] = {k_shrink_coop<0, true>, k_shrink_coop<1, true>};

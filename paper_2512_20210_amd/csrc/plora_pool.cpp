@@ -74,7 +74,9 @@ struct plora_batch {
   plora_pool* pool = nullptr;
   bool open = false;
   bool panel = false;  // expand: the matrix-core blocks go to the panel kernel
-  bool panel_shrink = false;       // shrink: the list holds panel items (kind 2)
+  // shrink: panel items (kind 2) of the list, those of more than kMfmaRows rows, and their tiles of tokens
+  int64_t panel_tiles = 0, panel_tall = 0, panel_tok = 0;
+  int32_t cut_blocks = 0;          // shrink: blocks of the list for launches that those would not fill the GPU with (0 = there is none)
   bool full_shrink_tiles = false;  // shrink: the matrix-core items average at least half a token tile
   hipStream_t stream = nullptr;
   int32_t n_tokens = 0, n_seg = 0, n_perm = 0;
@@ -96,8 +98,10 @@ struct plora_batch {
   // first (for launches whose fastest grid dimension is the slot), 1 = dealt into 8 interleaved XCD
   // queues
   // 2 = every group as vector-ALU records, one record per workgroup (cooperative kernels of small calls)
-  size_t off_items[2][3] = {{0, 0, 0}, {0, 0, 0}};
-  int32_t n_items[2][3] = {{0, 0, 0}, {0, 0, 0}};
+  // 3 (shrink) = without panel items, for small launches of a batch that has them; its first n_lone blocks are one record each
+  size_t off_items[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+  int32_t n_items[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+  int32_t n_lone = 0;
   int32_t n_heavy[2] = {0, 0};  // layout 0 only: records of the leading matrix-core blocks
   std::vector<int32_t> adapters;      // pinned adapters
   std::shared_ptr<Event> done;        // recorded by plora_batch_end; the images are reusable once it has passed
@@ -136,11 +140,8 @@ struct plora_pool {
   int panel_min_blocks = 8;  // expand: a batch with at least this many 64-token blocks of large groups (prefill) sends its
                              // matrix-core blocks to the panel kernel; other batches cut every large group into
                              // column-split items (0 = never)
-  // shrink: a batch with at least this many panel tiles (64 tokens x 64 rows of A) uses them (0 = always, -1 = never).
-  // A panel item's chain is d_in / 64 steps against a split item's d_in / 256, so launches that do not fill the GPU
-  // lose: 512 tokens over 8 adapters, one layer in calls of 3 + 1 slots, 35 us against 26 (8 - 12 tiles), 1,024 tokens 39
-  // against 38, 2,048 tokens 40 against 40 (32 or more); 2,048 tokens of ranks 8 / 16 in calls of 4 slots 17 against 20,
-  // 5,120 tokens 37 against 53.
+  // shrink: a batch with at least this many panel tiles (64 tokens x 64 rows of A) has a list with them for its launches to
+  // choose (panel_pays; 0 = any batch with one, and every launch takes it; -1 = never)
   int panel_min_tiles_shrink = 32;
   bool panel_shrink_fits = false;  // the page-table window holds the rows of a panel item
   int64_t panel_half_max_workgroups = 8192;  // expand: a panel launch of at most this many workgroups (of 512 columns) is
@@ -150,8 +151,8 @@ struct plora_pool {
   int open_batches = 0;
   std::vector<int32_t> count, cursor;              // per-adapter scratch of the counting sort
   // scratch of the work-list construction (capacity kept from batch to batch)
-  ItemGroups wl[2][2];                             // [op][0 vector-ALU | 1 matrix-core]
-  std::vector<ItemRec> wl_lists[2][3], wl_tg;
+  ItemGroups wl[2][2], wl_cut;                     // [op][0 vector-ALU | 1 matrix-core]; the latter without panel items (shrink)
+  std::vector<ItemRec> wl_lists[2][4], wl_tg;
   std::vector<uint32_t> wl_bucket;
   std::vector<int32_t> wl_touched;
   // tunables
@@ -277,17 +278,22 @@ void append_by_rank(const std::vector<ItemRec>& src, const uint32_t* idx, size_t
 // Matrix-core blocks first (their dependent chains are the long ones).  With xcd_aware the groups
 // are dealt into 8 queues (longest first, each to the least loaded queue) and the queues are
 // interleaved block by block; queues that run out are padded with empty blocks.
+// With n_lone the matrix-core blocks are one record each, without the padding, ahead of all others (*n_lone of them, empty ones
+// included): a second list of a batch costs a quarter of the image that way.
 void arrange_blocks(const ItemGroups& heavy, const ItemGroups& light, bool xcd_aware, std::vector<ItemRec>& out,
-                    std::vector<uint32_t>& bucket, int32_t* n_heavy_records = nullptr) {
+                    std::vector<uint32_t>& bucket, int32_t* n_heavy_records = nullptr, int32_t* n_lone = nullptr) {
   out.clear();
   ItemRec pad{};
   pad.kind = -1;
+  const int per_heavy = n_lone ? 1 : 4;  // records of a matrix-core block
   if (!xcd_aware) {
-    out.reserve(4 * heavy.items.size() + light.items.size() + 4);
-    for (const ItemRec& it : heavy.items) { out.push_back(it); out.insert(out.end(), 3, pad); }
+    out.reserve(per_heavy * heavy.items.size() + light.items.size() + 4);
+    for (const ItemRec& it : heavy.items) { out.push_back(it); out.insert(out.end(), per_heavy - 1, pad); }
+    const size_t n = out.size();
     append_by_rank(light.items, nullptr, light.items.size(), out, bucket);
-    while (out.size() % 4) out.push_back(pad);
-    if (n_heavy_records) *n_heavy_records = (int32_t)(4 * heavy.items.size());
+    while ((out.size() - n) % 4) out.push_back(pad);
+    if (n_heavy_records) *n_heavy_records = (int32_t)n;
+    if (n_lone) *n_lone = (int32_t)n;
     return;
   }
   if (n_heavy_records) *n_heavy_records = 0;
@@ -308,6 +314,14 @@ void arrange_blocks(const ItemGroups& heavy, const ItemGroups& light, bool xcd_a
   };
   deal(heavy, qh);
   deal(light, ql);
+  if (n_lone) {
+    size_t rows = 0;
+    for (int k = 0; k < nq; ++k) rows = std::max(rows, qh[k].size());
+    for (size_t i = 0; i < rows; ++i)
+      for (int k = 0; k < nq; ++k) out.push_back(i < qh[k].size() ? heavy.items[qh[k][i]] : pad);
+    *n_lone = (int32_t)out.size();
+    for (int k = 0; k < nq; ++k) qh[k].clear();
+  }
   std::vector<ItemRec> blocks[nq];  // per queue, 4 records per block
   size_t longest = 0;
   for (int k = 0; k < nq; ++k) {
@@ -317,7 +331,7 @@ void arrange_blocks(const ItemGroups& heavy, const ItemGroups& light, bool xcd_a
     while (blocks[k].size() % 4) blocks[k].push_back(pad);
     longest = std::max(longest, blocks[k].size() / 4);
   }
-  out.reserve(longest * 4 * nq);
+  out.reserve(out.size() + longest * 4 * nq);
   for (size_t i = 0; i < longest; ++i)
     for (int k = 0; k < nq; ++k)
       for (int w = 0; w < 4; ++w) out.push_back(4 * i + w < blocks[k].size() ? blocks[k][4 * i + w] : pad);
@@ -866,6 +880,29 @@ int plora_pool_set_option(plora_pool* p, const char* key, int64_t value) {
 // ---------------------------------------------------------------------------------------------
 // batch translation
 // ---------------------------------------------------------------------------------------------
+// Whether a shrink launch over nq slots takes a batch's panel items: their chain is d_in / 64 steps of one workgroup, a split item's
+// d_in / 256, so they have to fill the GPU; and what they save is x, read once for 64 rows instead of 32, and once for
+// slots side by side that share it (`shared`, as q, k, v do) or for the parts of a rank above 64.  Measured, us a launch of panel
+// and of split items, d_in 4096:
+//   q, k, v, o, tiles x slots 128: rank 16 17.5 / 16.2, rank 64 23.6 / 22.9, of d_in 13824 88 / 66; 192: 19.4 / 22.1, 24.2 / 28.9,
+//   98 / 102; 256: 18.7 / 23.5, 32.1 / 37.4, 107 / 136;
+//   one slot, rank 128: 64 tiles 22.0 / 16.0, 128 23.1 / 21.0, 192 24.1 / 27.1; rank 64 (several slots that share nothing are like one): 64
+//   22.5 / 16.5, 128 23.7 / 22.3, 192 37.3 / 33.3, 256 37.4 / 42.3, 384 57.6 / 63.2, of d_in 13824 88 / 41, 99 / 77, 108 / 114, 121 / 151,
+//   191 / 223; ranks up to 32, whose x split items read no more often: 256 33.5 / 27.8, 512 62 / 51, 1024 121 / 103.
+static bool panel_pays(const plora_batch* b, int nq, bool shared) {
+  const int64_t workgroups = b->panel_tiles * nq;
+  if (shared || 2 * b->panel_tiles >= 3 * b->panel_tok) return workgroups >= 192;
+  return workgroups >= 256 && 2 * b->panel_tall >= b->panel_tiles;
+}
+
+// The limit of the cooperative shrink.  In a batch with panel items it is at most 64, against the blocks of the list without
+// them: 64 blocks (one slot, 2,048 tokens of rank 16, d_in 4096) 11.4 us against 14.4 as split items, 96 15.6 against 15.1, 128
+// (rank 64) 26.6 against 15.2.
+constexpr int64_t kCoopMaxPanelBatch = 64;
+static int64_t coop_max_shrink(const plora_pool* p, const plora_batch* b) {
+  return b->panel_tiles > 0 ? std::min(p->coop_max_workgroups[0], kCoopMaxPanelBatch) : p->coop_max_workgroups[0];
+}
+
 // Queues the transfer of a batch's image and the batch stream's waits for adapters that are still loading.  If that fails,
 // what was queued so far may still read the page-locked image and write the device's: the object then gets a
 // marker behind it, as at the end of a batch.
@@ -1017,14 +1054,21 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     if (!half) return f32_items >= kF32MinItems && n >= min_tokens_s;
     return n >= min_tokens_s || (int64_t)n * a.rank >= p->mfma_min_work;
   };
-  int64_t panel_tiles = 0;
-  for (int32_t u = 0; u < n_seg && p->panel_min_tiles_shrink >= 0 && p->panel_shrink_fits; ++u) {
+  b->panel_tiles = b->panel_tall = b->panel_tok = 0;
+  for (int32_t u = 0; u < n_seg && half && p->panel_min_tiles_shrink >= 0 && p->panel_shrink_fits; ++u) {
     const int32_t n = p->count[touched[u]];
     const Adapter& a = p->ad[touched[u]];
-    if (shrink_on_matrix_cores(a, n))
-      panel_tiles += (int64_t)(n / kPanelTokS + (n % kPanelTokS > kMfmaTokS)) * ((a.rank + kPanelRowsS - 1) / kPanelRowsS);
+    if (!shrink_on_matrix_cores(a, n)) continue;
+    const int64_t tok_tiles = n / kPanelTokS + (n % kPanelTokS > kMfmaTokS);
+    b->panel_tok += tok_tiles;
+    b->panel_tiles += tok_tiles * ((a.rank + kPanelRowsS - 1) / kPanelRowsS);
+    b->panel_tall += tok_tiles * ((a.rank + kPanelRowsS - 1 - kMfmaRows) / kPanelRowsS);
   }
-  b->panel_shrink = half && panel_tiles > 0 && panel_tiles >= p->panel_min_tiles_shrink;
+  if (b->panel_tiles < p->panel_min_tiles_shrink) b->panel_tiles = 0;
+  const bool panel_shrink = b->panel_tiles > 0;
+  // another list for the launches that will not take the panel items, if there can be such
+  const bool cut = panel_shrink && p->panel_min_tiles_shrink > 0 && !panel_pays(b, 1, false);
+  p->wl_cut.clear();
   const int32_t cols_max_group = b->panel ? p->cols_max_group : kTokBlock;
   size_t n_pt_total = 0;
   int64_t mfma_shrink_items = 0, mfma_shrink_tokens = 0;
@@ -1051,7 +1095,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
         const int16_t kind = (int16_t)((n <= kMfmaTokS ? 1 | kItemOnce : 1) | contig);
         // panel items first: whole tiles of tokens, and a last one that is more than half full
         int32_t bp = b0;
-        if (b->panel_shrink) bp += (b1 - b0) / kPanelTokS * kPanelTokS + ((b1 - b0) % kPanelTokS > kMfmaTokS ? (b1 - b0) % kPanelTokS : 0);
+        if (panel_shrink) bp += (b1 - b0) / kPanelTokS * kPanelTokS + ((b1 - b0) % kPanelTokS > kMfmaTokS ? (b1 - b0) % kPanelTokS : 0);
         const int16_t pkind = (int16_t)((n <= kPanelTokS ? 2 | kItemOnce : 2) | contig);
         for (int32_t j0 = 0; j0 < a.rank && bp > b0; j0 += kPanelRowsS)
           for (int32_t t0 = b0; t0 < bp; t0 += kPanelTokS) {
@@ -1059,15 +1103,19 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
             wl[0][1].items.push_back(ItemRec{pkind, nt, rank, (int16_t)j0, a.scale, pt_off, {start + t0, 0, 0, 0}});
             cost += std::min(kPanelRowsS, a.rank - j0) + nt;
           }
-        for (int32_t j0 = 0; j0 < a.rank; j0 += kMfmaRows)
-          for (int32_t t0 = bp; t0 < b1; t0 += kMfmaTokS) {
-            const int16_t nt = (int16_t)std::min(kMfmaTokS, b1 - t0);
-            ++mfma_shrink_items;
-            mfma_shrink_tokens += nt;
-            wl[0][1].items.push_back(ItemRec{kind, nt, rank, (int16_t)j0, a.scale, pt_off, {start + t0, 0, 0, 0}});
-            cost += std::min(kMfmaRows, a.rank - j0) + nt;
-          }
-        wl[0][1].close_group(cost);
+        auto split_items = [&](ItemGroups& dst, int32_t first, double cost) {
+          for (int32_t j0 = 0; j0 < a.rank; j0 += kMfmaRows)
+            for (int32_t t0 = first; t0 < b1; t0 += kMfmaTokS) {
+              const int16_t nt = (int16_t)std::min(kMfmaTokS, b1 - t0);
+              ++mfma_shrink_items;
+              mfma_shrink_tokens += nt;
+              dst.items.push_back(ItemRec{kind, nt, rank, (int16_t)j0, a.scale, pt_off, {start + t0, 0, 0, 0}});
+              cost += std::min(kMfmaRows, a.rank - j0) + nt;
+            }
+          dst.close_group(cost);
+        };
+        split_items(wl[0][1], bp, cost);
+        if (cut) split_items(p->wl_cut, b0, 0.0);
       }
       if (mf_e) {
         double cost = 0.0;
@@ -1119,7 +1167,14 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     none_groups(wl[0][0].items);
     wl[0][0].close_group(0.1 * ((n_none + kValuTok - 1) / kValuTok));
   }
-  std::vector<ItemRec>(&lists)[2][3] = p->wl_lists;  // [op][layout]
+  std::vector<ItemRec>(&lists)[2][4] = p->wl_lists;  // [op][layout]
+  lists[0][3].clear();
+  lists[1][3].clear();
+  b->cut_blocks = b->n_lone = 0;
+  if (cut) {
+    arrange_blocks(p->wl_cut, wl[0][0], p->xcd_remap[0] != 0, lists[0][3], p->wl_bucket, nullptr, &b->n_lone);
+    b->cut_blocks = (int32_t)(b->n_lone + (lists[0][3].size() - b->n_lone) / 4);
+  }
   for (int op = 0; op < 2; ++op) {
     arrange_blocks(wl[op][1], wl[op][0], false, lists[op][0], p->wl_bucket, &b->n_heavy[op]);
     // the XCD-dealt form only if launches may ask for it
@@ -1131,8 +1186,10 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     const int64_t min_grid = op == 1 ? p->min_chunks : 1;  // workgroups per block of the list in the smallest launch
     // (an expand panel batch: the groups that do not go to the panel kernel)
     const bool light_only = op == 1 && b->panel;
-    const int64_t blocks = (int64_t)((lists[op][0].size() - (light_only ? b->n_heavy[1] : 0)) / 4);
-    if (!(op == 0 && b->panel_shrink) && p->coop_max_workgroups[op] > 0 && blocks * min_grid <= p->coop_max_workgroups[op]) {
+    const int64_t blocks = op == 0 && panel_shrink ? b->cut_blocks
+                                                   : (int64_t)((lists[op][0].size() - (light_only ? b->n_heavy[1] : 0)) / 4);
+    const int64_t coop_max = op == 0 ? coop_max_shrink(p, b) : p->coop_max_workgroups[1];
+    if (coop_max > 0 && blocks > 0 && blocks * min_grid <= coop_max) {
       std::vector<ItemRec>& all = wl[op][1].items;  // reused as scratch: the matrix-core records are arranged already
       all.clear();
       size_t pt_run = 0;
@@ -1161,7 +1218,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
   b->off_perm = off; off = align_up(off + (size_t)T * 4, 256);
   b->off_pt = off; off = align_up(off + (n_pt_total + 1) * 4, 256);
   for (int op = 0; op < 2; ++op)
-    for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < 4; ++k) {
       b->off_items[op][k] = off; b->n_items[op][k] = (int32_t)lists[op][k].size();
       off = align_up(off + lists[op][k].size() * sizeof(ItemRec), 256);
     }
@@ -1195,7 +1252,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     *dst = 0;
   }
   for (int op = 0; op < 2; ++op)
-    for (int k = 0; k < 3; ++k)
+    for (int k = 0; k < 4; ++k)
       if (!lists[op][k].empty())
         std::memcpy(b->h_img + b->off_items[op][k], lists[op][k].data(), lists[op][k].size() * sizeof(ItemRec));
   b->perm.resize(n_perm);
@@ -1245,7 +1302,6 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
   a.elems_per_rank = p->C;
   const int vec = 16 / p->elt;
   const int op = is_shrink ? 0 : 1;
-  a.pad0 = 0;
   // Launch classes: an expand launch has one grid dimension for the 512-column chunks, so slots with
   // different chunk counts go in launches of their own (no empty workgroups) ...; shrink has one class.
   std::pair<int, int>* order = p->run_order.data();  // (chunks, index within the call), stable by chunks
@@ -1296,9 +1352,16 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     const bool panel = op == 1 && b->panel && b->n_heavy[1] > 0;
     int layout = (!panel && a.slot_fastest != 1 && p->xcd_remap[op] && b->n_items[op][1] > 0) ? 1 : 0;
     // a call that cannot fill the machine is bound by its longest dependent chain: cooperative kernels
-    const bool coop = !panel && p->coop_max_workgroups[op] > 0 && b->n_items[op][2] > 0 &&
-                      (int64_t)nq * (b->n_items[op][layout] / 4) * chunks <= p->coop_max_workgroups[op];
+    const bool panel_shrink = is_shrink && b->panel_tiles > 0;
+    const int64_t blocks = panel_shrink ? b->cut_blocks : b->n_items[op][layout] / 4;
+    const int64_t coop_max = is_shrink ? coop_max_shrink(p, b) : p->coop_max_workgroups[1];
+    const bool coop = !panel && coop_max > 0 && b->n_items[op][2] > 0 && nq * blocks * chunks <= coop_max;
+    int same = 0;  // slots that read the x of the slot before them
+    for (int q = 1; q < nq && panel_shrink; ++q) same += ptrs.a[q] == ptrs.a[q - 1];
+    const bool cut = panel_shrink && b->cut_blocks > 0 && !panel_pays(b, nq, 4 * same >= nq);
     if (coop) layout = 2;
+    else if (cut) { layout = 3; a.slot_fastest = 0; }
+    a.n_lone = layout == 3 ? b->n_lone : 0;
     const ItemRec* list = (const ItemRec*)(b->d_img + b->off_items[op][layout]);
     const int n_all = b->n_items[op][layout];
     if (n_all == 0) continue;
@@ -1309,7 +1372,7 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
       int32_t max_in = 0;
       for (int q = 0; q < nq; ++q) max_in = std::max(max_in, p->slots[ptrs.slot[q]].d_in);
       // ... or a launch too small to hide the chain of an item's runs behind other workgroups
-      const bool small_launch = (int64_t)nq * (n_all / 4) <= p->deep_max_workgroups;
+      const bool small_launch = nq * (cut ? b->cut_blocks : n_all / 4) <= p->deep_max_workgroups;
       deep = p->mfma_shrink_depth == 2 || (p->mfma_shrink_depth == 0 && (b->full_shrink_tiles || max_in > 4096 || small_launch));
     }
     // one launch over the whole block list, or (panel batches) the matrix-core blocks in the panel kernel
@@ -1324,7 +1387,7 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     // 2056 -> 520 .. 2056: expand 217 -> 157 us a step; 3,000 and 64 tokens of a 7B-shaped layer 136 -> 119)
     const bool light_coop = panel && n_all > b->n_heavy[op] && p->coop_max_workgroups[1] > 0 && b->n_items[1][2] > 0 &&
                             (int64_t)nq * ((n_all - b->n_heavy[op]) / 4) * chunks <= p->coop_max_workgroups[1];
-    const Part parts[2] = {{list, panel ? b->n_heavy[op] : n_all, panel ? panel_mode : coop ? kModeCoop : is_shrink && b->panel_shrink ? kModeShrinkPanel : deep ? kModeDeep
+    const Part parts[2] = {{list, panel ? b->n_heavy[op] : n_all, panel ? panel_mode : coop ? kModeCoop : panel_shrink && !cut ? kModeShrinkPanel : deep ? kModeDeep
                            : is_shrink && p->dtype == PLORA_F32 && b->n_heavy[0] == 0 ? kModeLight : kModeBlocks},
                            light_coop ? Part{(const ItemRec*)(b->d_img + b->off_items[1][2]), b->n_items[1][2], kModeCoop}
                                       : Part{list + b->n_heavy[op], panel ? n_all - b->n_heavy[op] : 0, kModeBlocks}};
@@ -1371,7 +1434,7 @@ int plora_expand(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t n_s
 static int delta_in_one_launch(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t n_slots, const void* const* x,
                                float* const* v, void* const* y, plora_stream s) {
   if (p->fused_max_tasks <= 0 || n_slots > kMaxSlotsFused || (hipStream_t)s != b->stream || !b->d_queue) return 1;
-  if ((b->panel && b->n_heavy[1] > 0) || b->panel_shrink) return 1;
+  if ((b->panel && b->n_heavy[1] > 0) || b->panel_tiles > 0) return 1;
   {
     // a captured launch would be replayed with this call's counter targets: graphs take the two launches
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;

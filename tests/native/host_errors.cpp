@@ -20,6 +20,7 @@ int g_image_checks = 0;               // image kernels that have run
 hipStream_t g_image_stream = nullptr; // stream of the last one
 long g_fused_runs = 0;
 int g_items[2][3];                    // [op][kind]: records that the launches read
+int g_shrink_mode = -1, g_shrink_lone = 0;  // of the last launch
 }  // namespace
 
 namespace plora {
@@ -29,7 +30,14 @@ void count_items(int op, const LaunchArgs& a, hipStream_t st) {
       if (a.items[i].kind >= 0) { CHECK((a.items[i].kind & 0xff) < 3); ++g_items[op][a.items[i].kind & 0xff]; }
   });
 }
-hipError_t launch_shrink(int, const LaunchArgs& a, const SlotPtrs&, int, int, hipStream_t st, hipEvent_t, hipEvent_t) {
+hipError_t launch_shrink(int, const LaunchArgs& a, const SlotPtrs&, int, int mode, hipStream_t st, hipEvent_t, hipEvent_t) {
+  g_shrink_mode = mode;
+  g_shrink_lone = a.n_lone;
+  if (a.n_lone > 0)  // single records of matrix-core items (or padding), then whole blocks without
+    fakehip::enqueue_kernel(st, [=] {
+      CHECK(a.n_items >= a.n_lone && (a.n_items - a.n_lone) % 4 == 0);
+      for (int i = 0; i < a.n_items; ++i) CHECK(a.items[i].kind == -1 || ((a.items[i].kind & 0xff) > 0) == (i < a.n_lone));
+    });
   count_items(0, a, st);
   return hipSuccess;
 }
@@ -206,6 +214,48 @@ void fp32_thresholds() {
     CHECK((g_items[1][1] > 0) == w.mfma_e && (g_items[1][0] > 0) == !w.mfma_e);
   }
 }
+
+// A prefill shrink takes panel items as such where they fill the GPU and cuts them where they do not.
+void panel_route() {
+  enum { kPanel, kCut, kCoop, kOther };
+  struct { int rank, tiles, slots, distinct_x, limit, route; } want[] = {
+    {64, 47, 4, 2, 32, kCut},  {64, 48, 4, 2, 32, kPanel}, {16, 48, 4, 2, 32, kPanel},
+    {64, 255, 1, 1, 32, kCut}, {64, 256, 1, 1, 32, kPanel}, {16, 256, 1, 1, 32, kCut},
+    {64, 63, 4, 4, 32, kCut},  {64, 64, 4, 4, 32, kPanel},  {16, 64, 4, 4, 32, kCut},
+    {64, 1, 1, 1, 0, kPanel},  {16, 300, 8, 1, -1, kOther},           {64, 31, 4, 1, 32, kOther},
+    {128, 190, 1, 1, 32, kCut},          {128, 192, 1, 1, 32, kPanel},          {16, 32, 1, 1, 32, kCoop},           {16, 40, 1, 1, 32, kCut},
+  };
+  for (auto& w : want) {
+    const int n_slots = 8;
+    const std::vector<int32_t> d(n_slots, 64);
+    plora_layout lay{n_slots, d.data(), d.data(), PLORA_BF16, 2, 128};
+    plora_pool* p = nullptr;
+    CHECK(plora_pool_create(4096, 128, &lay, nullptr, 0, &p) == PLORA_OK);
+    CHECK(plora_pool_set_option(p, "panel_min_tiles_shrink", w.limit) == PLORA_OK);
+    hipStream_t st = nullptr;
+    CHECK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess);
+    void* blob = nullptr;
+    CHECK(hipHostMalloc(&blob, plora_adapter_bytes(p, 128), 0) == hipSuccess);
+    std::memset(blob, 0, plora_adapter_bytes(p, 128));
+    CHECK(plora_load_adapter(p, 0, w.rank, 1.f, blob, st, nullptr, nullptr) == PLORA_OK);
+    std::vector<int32_t> t2a((size_t)w.tiles * 64 / (w.rank > 64 ? 2 : 1), 0);
+    if (w.route != kCoop) t2a.resize(t2a.size() + 5, 0), t2a[0] = -1;  // some tokens for items of other kinds
+    plora_batch* b = nullptr;
+    CHECK(plora_batch_begin(p, t2a.data(), (int32_t)t2a.size(), st, &b) == PLORA_OK);
+    std::vector<const void*> x(n_slots);
+    std::vector<float*> v(n_slots, (float*)0x1000);
+    for (int q = 0; q < n_slots; ++q) x[q] = (const void*)(uintptr_t)(0x10000 + 256 * (q * w.distinct_x / w.slots));
+    CHECK(plora_shrink(p, b, 0, w.slots, x.data(), v.data(), st) == PLORA_OK);
+    CHECK(plora_batch_end(p, b) == PLORA_OK);
+    fakehip::drain();
+    std::printf("rank %d, %d tiles, %d slots reading %d x, limit %d: mode %d, %d single records\n", w.rank, w.tiles, w.slots, w.distinct_x, w.limit, g_shrink_mode,
+                g_shrink_lone);
+    const int route = g_shrink_mode == plora::kModeShrinkPanel ? kPanel : g_shrink_mode == plora::kModeCoop ? kCoop : g_shrink_lone > 0 ? kCut : kOther;
+    CHECK(route == w.route);
+    CHECK(plora_pool_destroy(p) == PLORA_OK);
+    CHECK(hipHostFree(blob) == hipSuccess && hipStreamDestroy(st) == hipSuccess);
+  }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -215,6 +265,7 @@ int main(int argc, char** argv) {
     else if (name == "callers_error") callers_error();
     else if (name == "counters_cleared") counters_cleared();
     else if (name == "fp32_thresholds") fp32_thresholds();
+    else if (name == "panel_route") panel_route();
     else return 2;
     std::printf("%s OK\n", name.c_str());
   }
