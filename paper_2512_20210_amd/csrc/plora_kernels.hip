@@ -1474,6 +1474,19 @@ __global__ __launch_bounds__(256, kWgPerCu) void k_shrink(const LaunchArgs a, co
       return;
     }
   }
+  if constexpr (DT == 2 && DEPTH == 0) {
+    if (item_kind(first) == 3) {
+      const int t = wave_id() * kValuTok;
+      if (t >= first.ntok) return;
+      ItemRec it = first;
+      it.kind = (int16_t)(first.kind & kItemContig);
+      it.ntok = (int16_t)imin(first.ntok - t, kValuTok);
+#pragma unroll
+      for (int i = 0; i < kValuTok; ++i) it.tok[i] = a.perm[first.tok[0] + t + imin(i, it.ntok - 1)];
+      shrink_valu_item<DT>(a, it, sl, x, v, lds_pt + wave_id() * (kPtWindow / 4));
+      return;
+    }
+  }
   if (lone) return;  // padding
   const int wave = wave_id();
   const ItemRec it = load_item(rec + wave);

@@ -76,6 +76,7 @@ struct plora_batch {
   bool panel = false;  // expand: the matrix-core blocks go to the panel kernel
   // shrink: panel items (kind 2) of the list, those of more than kMfmaRows rows, and their tiles of tokens
   int64_t panel_tiles = 0, panel_tall = 0, panel_tok = 0;
+  int64_t f32_items = 0;           // fp32 shrink: matrix-core items of the list
   int32_t cut_blocks = 0;          // shrink: blocks of the list for launches that those would not fill the GPU with (0 = there is none)
   bool full_shrink_tiles = false;  // shrink: the matrix-core items average at least half a token tile
   hipStream_t stream = nullptr;
@@ -98,7 +99,8 @@ struct plora_batch {
   // first (for launches whose fastest grid dimension is the slot), 1 = dealt into 8 interleaved XCD
   // queues
   // 2 = every group as vector-ALU records, one record per workgroup (cooperative kernels of small calls)
-  // 3 (shrink) = without panel items, for small launches of a batch that has them; its first n_lone blocks are one record each
+  // 3 (shrink) = without panel items, or in fp32 without matrix-core ones, for small launches of a batch that has them; its
+  // first n_lone blocks are one record each
   size_t off_items[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
   int32_t n_items[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
   int32_t n_lone = 0;
@@ -222,11 +224,7 @@ int poll_ready(plora_pool* p, Adapter& a) {
 // Groups take matrix-core items from this many tokens on, [shrink, expand] ...
 constexpr int kMinTokens[2] = {16, 64};
 constexpr int kF32MinTokens = 16;  // (fp32 pools, both)
-// ... in fp32 shrink only if the batch has at least this many such items: an item's products alone are 28 us on its four
-// SIMDs at d_in 4096, so a few items are a longer chain than the vector-ALU items they replace (256 tokens over 64
-// adapters, 4 slots 4096 -> 4096 a call: 36 us a launch with vector-ALU items, 43 - 50 with 8 matrix-core items; 1,024
-// tokens in calls of 3 + 1 slots, about 40 items: 346 against 327 us on average and 275 against 363 at worst; 2,048
-// tokens of prefill 2048 -> 2048, 64 items or more: 107 against 36).
+// ... in fp32 shrink only in a batch of at least this many such items; its launches then decide, see f32_pays.
 constexpr int64_t kF32MinItems = 64;
 // Batch images up to this size go by a kernel.  One projection of 16 tokens takes 21 us a step that way and 43 with the
 // side stream, a prefill of 5,120 tokens 131 either way, and 161 against 183 when the step starts on an idle GPU.  A
@@ -895,6 +893,13 @@ static bool panel_pays(const plora_batch* b, int nq, bool shared) {
   return workgroups >= 256 && 2 * b->panel_tall >= b->panel_tiles;
 }
 
+// Whether an fp32 shrink launch over nq slots takes a batch's matrix-core items: a lone item's products and their chain are some 32 us
+// at d_in 4096, so few of them lose against the vector-ALU items of the same work, which are many and short.  Measured, us a
+// launch of matrix-core and of vector-ALU items, d_in 4096, items x slots 64: 41 / 20 (rank 64) and 32 / 20 (rank 16), 128: 42 / 32 and 33 / 23, 192:
+// 42 / 47 and 33 / 29, 256: 41 / 56 and 35 / 40, 384: 68 / 99 and 57 / 58, 512: 71 / 142 and 63 / 81; d_in 1024: 15 / 9, 16 / 12, 15 / 16, 14 / 19,
+// 23 / 27, 23 / 34.
+static bool f32_pays(const plora_batch* b, int nq) { return b->f32_items * nq >= 256; }
+
 // The limit of the cooperative shrink.  In a batch with panel items it is at most 64, against the blocks of the list without
 // them: 64 blocks (one slot, 2,048 tokens of rank 16, d_in 4096) 11.4 us against 14.4 as split items, 96 15.6 against 15.1, 128
 // (rank 64) 26.6 against 15.2.
@@ -1043,15 +1048,16 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
   b->panel = half && p->panel_min_blocks > 0 && panel_blocks >= p->panel_min_blocks;
   // fp32: matrix-core shrink items only in a batch with many of them, see kF32MinItems (a threshold that was set asks for
   // them in any batch)
-  int64_t f32_items = p->mfma_min_tokens >= 0 ? kF32MinItems : 0;
+  const bool f32_any = p->mfma_min_tokens >= 0;
+  b->f32_items = 0;
   for (int32_t u = 0; u < n_seg && !half; ++u) {
     const int32_t n = p->count[touched[u]];
     if (n >= min_tokens_s)
-      f32_items += (int64_t)((n + kMfmaTokS - 1) / kMfmaTokS) * ((p->ad[touched[u]].rank + kMfmaRows - 1) / kMfmaRows);
+      b->f32_items += (int64_t)((n + kMfmaTokS - 1) / kMfmaTokS) * ((p->ad[touched[u]].rank + kMfmaRows - 1) / kMfmaRows);
   }
   auto shrink_on_matrix_cores = [&](const Adapter& a, int32_t n) {
     if (min_tokens_s <= 0) return false;
-    if (!half) return f32_items >= kF32MinItems && n >= min_tokens_s;
+    if (!half) return n >= min_tokens_s && (f32_any || b->f32_items >= kF32MinItems);
     return n >= min_tokens_s || (int64_t)n * a.rank >= p->mfma_min_work;
   };
   b->panel_tiles = b->panel_tall = b->panel_tok = 0;
@@ -1066,8 +1072,9 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
   }
   if (b->panel_tiles < p->panel_min_tiles_shrink) b->panel_tiles = 0;
   const bool panel_shrink = b->panel_tiles > 0;
-  // another list for the launches that will not take the panel items, if there can be such
-  const bool cut = panel_shrink && p->panel_min_tiles_shrink > 0 && !panel_pays(b, 1, false);
+  // another list for the launches that will not take these items, if there can be such
+  const bool cut = half ? panel_shrink && p->panel_min_tiles_shrink > 0 && !panel_pays(b, 1, false)
+                        : !f32_any && min_tokens_s > 0 && b->f32_items >= kF32MinItems && !f32_pays(b, 1);
   p->wl_cut.clear();
   const int32_t cols_max_group = b->panel ? p->cols_max_group : kTokBlock;
   size_t n_pt_total = 0;
@@ -1115,7 +1122,17 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
           dst.close_group(cost);
         };
         split_items(wl[0][1], bp, cost);
-        if (cut) split_items(p->wl_cut, b0, 0.0);
+        if (cut && half) split_items(p->wl_cut, b0, 0.0);
+        if (cut && !half) {  // token groups innermost, as in the vector-ALU list
+          double vec_cost = 0.0;
+          for (int32_t j0 = 0; j0 < a.rank; j0 += kShrinkRows)
+            for (int32_t t0 = b0; t0 < b1; t0 += kVecBlockTok) {
+              const int16_t nt = (int16_t)std::min(kVecBlockTok, b1 - t0);
+              p->wl_cut.items.push_back(ItemRec{(int16_t)(3 | contig), nt, rank, (int16_t)j0, a.scale, pt_off, {start + t0, 0, 0, 0}});
+              vec_cost += std::min(kShrinkRows, a.rank - j0) + nt;
+            }
+          p->wl_cut.close_group(vec_cost);
+        }
       }
       if (mf_e) {
         double cost = 0.0;
@@ -1186,7 +1203,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     const int64_t min_grid = op == 1 ? p->min_chunks : 1;  // workgroups per block of the list in the smallest launch
     // (an expand panel batch: the groups that do not go to the panel kernel)
     const bool light_only = op == 1 && b->panel;
-    const int64_t blocks = op == 0 && panel_shrink ? b->cut_blocks
+    const int64_t blocks = op == 0 && (panel_shrink || cut) ? b->cut_blocks
                                                    : (int64_t)((lists[op][0].size() - (light_only ? b->n_heavy[1] : 0)) / 4);
     const int64_t coop_max = op == 0 ? coop_max_shrink(p, b) : p->coop_max_workgroups[1];
     if (coop_max > 0 && blocks > 0 && blocks * min_grid <= coop_max) {
@@ -1353,12 +1370,12 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     int layout = (!panel && a.slot_fastest != 1 && p->xcd_remap[op] && b->n_items[op][1] > 0) ? 1 : 0;
     // a call that cannot fill the machine is bound by its longest dependent chain: cooperative kernels
     const bool panel_shrink = is_shrink && b->panel_tiles > 0;
-    const int64_t blocks = panel_shrink ? b->cut_blocks : b->n_items[op][layout] / 4;
+    const int64_t blocks = is_shrink && (panel_shrink || b->cut_blocks > 0) ? b->cut_blocks : b->n_items[op][layout] / 4;
     const int64_t coop_max = is_shrink ? coop_max_shrink(p, b) : p->coop_max_workgroups[1];
     const bool coop = !panel && coop_max > 0 && b->n_items[op][2] > 0 && nq * blocks * chunks <= coop_max;
     int same = 0;  // slots that read the x of the slot before them
     for (int q = 1; q < nq && panel_shrink; ++q) same += ptrs.a[q] == ptrs.a[q - 1];
-    const bool cut = panel_shrink && b->cut_blocks > 0 && !panel_pays(b, nq, 4 * same >= nq);
+    const bool cut = is_shrink && b->cut_blocks > 0 && !(panel_shrink ? panel_pays(b, nq, 4 * same >= nq) : f32_pays(b, nq));
     if (coop) layout = 2;
     else if (cut) { layout = 3; a.slot_fastest = 0; }
     a.n_lone = layout == 3 ? b->n_lone : 0;
@@ -1368,7 +1385,7 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     // matrix-core shrink items keep two runs of k-values in flight where that pays: token tiles that
     // are mostly full (prefill), or a long contraction
     bool deep = false;
-    if (is_shrink && !coop && b->n_heavy[0] > 0) {
+    if (is_shrink && !coop && b->n_heavy[0] > 0 && !(cut && p->dtype == PLORA_F32)) {
       int32_t max_in = 0;
       for (int q = 0; q < nq; ++q) max_in = std::max(max_in, p->slots[ptrs.slot[q]].d_in);
       // ... or a launch too small to hide the chain of an item's runs behind other workgroups
@@ -1388,7 +1405,7 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     const bool light_coop = panel && n_all > b->n_heavy[op] && p->coop_max_workgroups[1] > 0 && b->n_items[1][2] > 0 &&
                             (int64_t)nq * ((n_all - b->n_heavy[op]) / 4) * chunks <= p->coop_max_workgroups[1];
     const Part parts[2] = {{list, panel ? b->n_heavy[op] : n_all, panel ? panel_mode : coop ? kModeCoop : panel_shrink && !cut ? kModeShrinkPanel : deep ? kModeDeep
-                           : is_shrink && p->dtype == PLORA_F32 && b->n_heavy[0] == 0 ? kModeLight : kModeBlocks},
+                           : is_shrink && p->dtype == PLORA_F32 && (cut || b->n_heavy[0] == 0) ? kModeLight : kModeBlocks},
                            light_coop ? Part{(const ItemRec*)(b->d_img + b->off_items[1][2]), b->n_items[1][2], kModeCoop}
                                       : Part{list + b->n_heavy[op], panel ? n_all - b->n_heavy[op] : 0, kModeBlocks}};
     plora_pool::ProfRec rec{op, nullptr, nullptr};
@@ -1449,7 +1466,8 @@ static int delta_in_one_launch(plora_pool* p, const plora_batch* b, int32_t slot
   FusedArgs f;
   // the same choice of lists as the separate launches make: cooperative records for the smallest calls
   const bool coop_s = p->coop_max_workgroups[0] > 0 && b->n_items[0][2] > 0 &&
-                      (int64_t)n_slots * (b->n_items[0][0] / 4) <= p->coop_max_workgroups[0];
+                      (int64_t)n_slots * (b->cut_blocks > 0 ? b->cut_blocks : b->n_items[0][0] / 4) <= p->coop_max_workgroups[0];
+  if (!coop_s && b->cut_blocks > 0 && !f32_pays(b, n_slots)) return 1;
   const bool coop_e = p->coop_max_workgroups[1] > 0 && b->n_items[1][2] > 0 &&
                       (int64_t)n_slots * (b->n_items[1][0] / 4) * chunks <= p->coop_max_workgroups[1];
   f.coop_s = coop_s; f.coop_e = coop_e;

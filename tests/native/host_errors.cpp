@@ -19,7 +19,7 @@ int g_image_fault_in = 0;             // > 0: that many launches from now, one i
 int g_image_checks = 0;               // image kernels that have run
 hipStream_t g_image_stream = nullptr; // stream of the last one
 long g_fused_runs = 0;
-int g_items[2][3];                    // [op][kind]: records that the launches read
+int g_items[2][4];                    // [op][kind]: records that the launches read
 int g_shrink_mode = -1, g_shrink_lone = 0;  // of the last launch
 }  // namespace
 
@@ -27,16 +27,18 @@ namespace plora {
 void count_items(int op, const LaunchArgs& a, hipStream_t st) {
   fakehip::enqueue_kernel(st, [=] {
     for (int i = 0; i < a.n_items; ++i)
-      if (a.items[i].kind >= 0) { CHECK((a.items[i].kind & 0xff) < 3); ++g_items[op][a.items[i].kind & 0xff]; }
+      if (a.items[i].kind >= 0) { CHECK((a.items[i].kind & 0xff) < 4); ++g_items[op][a.items[i].kind & 0xff]; }
   });
 }
-hipError_t launch_shrink(int, const LaunchArgs& a, const SlotPtrs&, int, int mode, hipStream_t st, hipEvent_t, hipEvent_t) {
+hipError_t launch_shrink(int dtype, const LaunchArgs& a, const SlotPtrs&, int, int mode, hipStream_t st, hipEvent_t, hipEvent_t) {
   g_shrink_mode = mode;
   g_shrink_lone = a.n_lone;
   if (a.n_lone > 0)  // single records of matrix-core items (or padding), then whole blocks without
     fakehip::enqueue_kernel(st, [=] {
       CHECK(a.n_items >= a.n_lone && (a.n_items - a.n_lone) % 4 == 0);
       for (int i = 0; i < a.n_items; ++i) CHECK(a.items[i].kind == -1 || ((a.items[i].kind & 0xff) > 0) == (i < a.n_lone));
+      for (int i = 0; i < a.n_lone; ++i) CHECK(a.items[i].kind == -1 || (a.items[i].kind & 0xff) == (dtype == PLORA_F32 ? 3 : 1));
+      CHECK(dtype != PLORA_F32 || mode == kModeLight);
     });
   count_items(0, a, st);
   return hipSuccess;
@@ -256,6 +258,48 @@ void panel_route() {
     CHECK(hipHostFree(blob) == hipSuccess && hipStreamDestroy(st) == hipSuccess);
   }
 }
+
+// The same for fp32 shrink: matrix-core items where they fill the GPU, vector-ALU blocks where they do not.
+void fp32_route() {
+  enum { kMatrix, kVector, kCoop };
+  struct { int adapters, tokens, rank, slots, set, route; } want[] = {
+    {16, 64, 64, 1, -1, kVector}, {16, 64, 64, 3, -1, kVector}, {16, 64, 64, 4, -1, kMatrix}, {16, 64, 64, 1, 16, kCoop},
+    {64, 16, 8, 2, -1, kCoop},    {64, 16, 8, 4, -1, kMatrix},  {15, 64, 64, 8, -1, kVector},  // (60 items: not in the list)
+    {16, 256, 64, 1, -1, kMatrix},
+  };
+  for (auto& w : want) {
+    const int n_slots = 8;
+    const std::vector<int32_t> d(n_slots, 64);
+    plora_layout lay{n_slots, d.data(), d.data(), PLORA_F32, w.adapters, 64};
+    plora_pool* p = nullptr;
+    CHECK(plora_pool_create(65536, 8 * w.adapters, &lay, nullptr, 0, &p) == PLORA_OK);
+    if (w.set >= 0) CHECK(plora_pool_set_option(p, "mfma_min_tokens", w.set) == PLORA_OK);
+    hipStream_t st = nullptr;
+    CHECK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess);
+    void* blob = nullptr;
+    CHECK(hipHostMalloc(&blob, plora_adapter_bytes(p, 64), 0) == hipSuccess);
+    std::memset(blob, 0, plora_adapter_bytes(p, 64));
+    std::vector<int32_t> t2a;
+    for (int i = 0; i < w.adapters; ++i) {
+      CHECK(plora_load_adapter(p, i, w.rank, 1.f, blob, st, nullptr, nullptr) == PLORA_OK);
+      t2a.insert(t2a.end(), (size_t)w.tokens, i);
+    }
+    plora_batch* b = nullptr;
+    std::memset(g_items, 0, sizeof(g_items));
+    CHECK(plora_batch_begin(p, t2a.data(), (int32_t)t2a.size(), st, &b) == PLORA_OK);
+    std::vector<const void*> x(n_slots, (const void*)0x10000);
+    std::vector<float*> v(n_slots, (float*)0x1000);
+    CHECK(plora_shrink(p, b, 0, w.slots, x.data(), v.data(), st) == PLORA_OK);
+    CHECK(plora_batch_end(p, b) == PLORA_OK);
+    fakehip::drain();
+    std::printf("%d adapters, %d tokens each, rank %d, %d slots: mode %d, %d single records\n", w.adapters, w.tokens, w.rank, w.slots, g_shrink_mode, g_shrink_lone);
+    const int route = g_shrink_mode == plora::kModeCoop ? kCoop : g_items[0][1] > 0 ? kMatrix : kVector;
+    CHECK(route == w.route);
+    CHECK(route != kVector || w.adapters == 15 || g_items[0][3] == w.adapters * w.tokens / 16 * w.rank / 8);
+    CHECK(plora_pool_destroy(p) == PLORA_OK);
+    CHECK(hipHostFree(blob) == hipSuccess && hipStreamDestroy(st) == hipSuccess);
+  }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -266,6 +310,7 @@ int main(int argc, char** argv) {
     else if (name == "counters_cleared") counters_cleared();
     else if (name == "fp32_thresholds") fp32_thresholds();
     else if (name == "panel_route") panel_route();
+    else if (name == "fp32_route") fp32_route();
     else return 2;
     std::printf("%s OK\n", name.c_str());
   }

@@ -29,7 +29,8 @@ def test_tile_edges(oracle_mod, d_in, d_out):
     case.close()
 
 
-@pytest.mark.parametrize("groups", [[200, 150, 90, 16], [900, 700, 500, 15]])  # below and above the limit of 64 items
+# below the limit of 64 items; above it, with launches of fewer than 256 (vector-ALU blocks of 16 tokens) and of more
+@pytest.mark.parametrize("groups", [[200, 150, 90, 16], [900, 700, 500, 15], [1500, 1300, 903, 17]])
 def test_own_choice(oracle_mod, groups):
     ranks = [16, 33, 8, 64]
     lay = Layout((264, 512), (136, 72), DT_F32)
