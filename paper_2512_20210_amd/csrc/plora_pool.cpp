@@ -908,6 +908,16 @@ static int64_t coop_max_shrink(const plora_pool* p, const plora_batch* b) {
   return b->panel_tiles > 0 ? std::min(p->coop_max_workgroups[0], kCoopMaxPanelBatch) : p->coop_max_workgroups[0];
 }
 
+// The limit of the cooperative expand.  For what a panel batch has besides its panel blocks it is at most 256, a workgroup a CU: with
+// another kernel ahead of it on the GPU a larger launch starts warm.  Measured, us of both kernels with the rest on the
+// cooperative and on the ordinary kernel: 2,048 and 16 tokens of rank 64, one slot -> 1024 (8 workgroups) 13.3 / 19.5, -> 4096, 3 slots (96) 33.0 / 36.9;
+// 640 and 64, 3 slots -> 1024 (96) 14.0 / 19.0; 2,048 and 128 of rank 16, 3 slots -> 4096 (768) 38.1 / 35.0, with 400 (one slot, 800) 27.3 / 23.7; 640 and 64
+// of rank 64, 16 slots -> 4096 (2048) 138 / 128, 2,048 and 400, 3 slots (2400) 137 / 129.
+constexpr int64_t kCoopMaxRest = 256;
+static int64_t coop_max_expand(const plora_pool* p, const plora_batch* b) {
+  return b->panel ? std::min(p->coop_max_workgroups[1], kCoopMaxRest) : p->coop_max_workgroups[1];
+}
+
 // Queues the transfer of a batch's image and the batch stream's waits for adapters that are still loading.  If that fails,
 // what was queued so far may still read the page-locked image and write the device's: the object then gets a
 // marker behind it, as at the end of a batch.
@@ -1205,7 +1215,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     const bool light_only = op == 1 && b->panel;
     const int64_t blocks = op == 0 && (panel_shrink || cut) ? b->cut_blocks
                                                    : (int64_t)((lists[op][0].size() - (light_only ? b->n_heavy[1] : 0)) / 4);
-    const int64_t coop_max = op == 0 ? coop_max_shrink(p, b) : p->coop_max_workgroups[1];
+    const int64_t coop_max = op == 0 ? coop_max_shrink(p, b) : coop_max_expand(p, b);
     if (coop_max > 0 && blocks > 0 && blocks * min_grid <= coop_max) {
       std::vector<ItemRec>& all = wl[op][1].items;  // reused as scratch: the matrix-core records are arranged already
       all.clear();
@@ -1371,7 +1381,7 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     // a call that cannot fill the machine is bound by its longest dependent chain: cooperative kernels
     const bool panel_shrink = is_shrink && b->panel_tiles > 0;
     const int64_t blocks = is_shrink && (panel_shrink || b->cut_blocks > 0) ? b->cut_blocks : b->n_items[op][layout] / 4;
-    const int64_t coop_max = is_shrink ? coop_max_shrink(p, b) : p->coop_max_workgroups[1];
+    const int64_t coop_max = is_shrink ? coop_max_shrink(p, b) : coop_max_expand(p, b);
     const bool coop = !panel && coop_max > 0 && b->n_items[op][2] > 0 && nq * blocks * chunks <= coop_max;
     int same = 0;  // slots that read the x of the slot before them
     for (int q = 1; q < nq && panel_shrink; ++q) same += ptrs.a[q] == ptrs.a[q - 1];
@@ -1399,11 +1409,9 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     const int panel_mode = panel && 2 * chunks <= 65535 &&
                                    (int64_t)nq * (b->n_heavy[op] / 4) * chunks <= p->panel_half_max_workgroups
                                ? kModePanelHalf : kModePanel;
-    // what a panel batch has besides (decode tokens in a batch with prefill) is as often too little to fill the GPU: the
-    // cooperative kernel under the same limit (900 prefill and 93 decode tokens, ranks up to 100, calls of 3 and 1 slots
-    // 2056 -> 520 .. 2056: expand 217 -> 157 us a step; 3,000 and 64 tokens of a 7B-shaped layer 136 -> 119)
-    const bool light_coop = panel && n_all > b->n_heavy[op] && p->coop_max_workgroups[1] > 0 && b->n_items[1][2] > 0 &&
-                            (int64_t)nq * ((n_all - b->n_heavy[op]) / 4) * chunks <= p->coop_max_workgroups[1];
+    // what a panel batch has besides (decode tokens in a batch with prefill) is as often too little to fill the GPU
+    const bool light_coop = panel && n_all > b->n_heavy[op] && coop_max > 0 && b->n_items[1][2] > 0 &&
+                            (int64_t)nq * ((n_all - b->n_heavy[op]) / 4) * chunks <= coop_max;
     const Part parts[2] = {{list, panel ? b->n_heavy[op] : n_all, panel ? panel_mode : coop ? kModeCoop : panel_shrink && !cut ? kModeShrinkPanel : deep ? kModeDeep
                            : is_shrink && p->dtype == PLORA_F32 && (cut || b->n_heavy[0] == 0) ? kModeLight : kModeBlocks},
                            light_coop ? Part{(const ItemRec*)(b->d_img + b->off_items[1][2]), b->n_items[1][2], kModeCoop}
