@@ -806,12 +806,11 @@ typedef __attribute__((address_space(3))) void lds_void;
 __device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(uintptr_t)(const lds_void*)p; }
 // 16 bytes per lane from memory into LDS at dst + 16 * lane (dst: a uniform LDS address).
 // In assembly because the compiler makes every later LDS read wait for all such loads, also those into other stages;
-// here a stage is waited for with wait_loads and a barrier.  (No output registers: nothing is in flight but LDS bytes.
-// No other instruction of these kernels reads m0.)
+// here a stage is waited for with wait_loads and a barrier.  (No output registers: nothing is in flight but LDS bytes.)
 template <bool NTW>
 __device__ __forceinline__ void load_to_lds(const uint8_t* src, uint32_t dst) {
-  if constexpr (NTW) asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" : : "v"(src), "s"(dst) : "memory");
-  else asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst) : "memory");
+  if constexpr (NTW) asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" : : "v"(src), "s"(dst) : "memory", "m0");
+  else asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst) : "memory", "m0");
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() {  // until at most N of the wavefront's vector memory accesses are in flight
