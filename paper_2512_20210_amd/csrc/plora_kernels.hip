@@ -807,11 +807,14 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(
 // 16 bytes per lane from memory into LDS at dst + 16 * lane (dst: a uniform LDS address).
 // In assembly because the compiler makes every later LDS read wait for all such loads, also those into other stages;
 // here a stage is waited for with wait_loads and a barrier.  (No output registers: nothing is in flight but LDS bytes.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"  // (m0 is a reserved register; naming it orders other writers of it)
 template <bool NTW>
 __device__ __forceinline__ void load_to_lds(const uint8_t* src, uint32_t dst) {
   if constexpr (NTW) asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" : : "v"(src), "s"(dst) : "memory", "m0");
   else asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 template <int N>
 __device__ __forceinline__ void wait_loads() {  // until at most N of the wavefront's vector memory accesses are in flight
   static_assert(N >= 0 && N < 64, "six bits");
