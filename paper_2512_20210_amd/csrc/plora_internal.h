@@ -142,9 +142,8 @@ hipError_t launch_delta_queue(int dtype, const FusedArgs& f, const FusedPtrs& p,
                               hipEvent_t e1 = nullptr);
 
 // Copies a batch's image, `bytes` bytes (a multiple of 16), from page-locked host memory (src: its device address) to the
-// device on `st`.  Weak: the host code is also linked without the kernels (its tests), and then sends the
-// image by a copy call.
-__attribute__((weak)) hipError_t launch_copy_image(const void* src, void* dst, size_t bytes, hipStream_t st);
+// device on `st`.
+hipError_t launch_copy_image(const void* src, void* dst, size_t bytes, hipStream_t st);
 
 // The library's static device array (plora_delta_static keeps v there): its size, and its address on
 // the current device (looked up once per device).

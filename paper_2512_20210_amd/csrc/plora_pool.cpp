@@ -925,7 +925,7 @@ static int send_image(plora_pool* p, plora_batch* b, size_t need, const std::vec
   // A small image goes by a kernel on the batch's own stream; a large one on the pool's side stream, where it
   // overlaps kernels already queued on `stream` (so does the first of a batch object, behind the clearing of
   // its counters, and that of a stream under capture, which has to stay out of the graph).
-  bool by_kernel = launch_copy_image && need <= kImageByKernel && b->queue_cleared;
+  bool by_kernel = need <= kImageByKernel && b->queue_cleared;
   if (by_kernel) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     const hipError_t e = hipStreamIsCapturing(b->stream, &capture);
