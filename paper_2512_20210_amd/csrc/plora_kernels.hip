@@ -1971,12 +1971,12 @@ __global__ __launch_bounds__(256) void k_scatter_pages(const uint8_t* __restrict
   }
 }
 
-// A batch's image, read straight from page-locked host memory.  A kernel and not a copy call because it can go on the
-// batch's own stream without a copy engine's start-up: of 16 KiB 6 us of host time and 15 us until a kernel behind it
-// has run, against 22 and 35 for a copy on a side stream with an event that the batch's stream waits for (256 KiB:
-// 6 and 19 against 22 and 35; 1 MiB: 6 and 33 against 23 and 49).
+// A batch's image, read straight from page-locked host memory, 16 bytes per thread.  A kernel and not a copy call because it can
+// go on the batch's own stream: no copy engine to start, no event and no wait between two streams (the step times of
+// both ways and the size up to which this one is taken stand at kImageByKernel).
 __global__ __launch_bounds__(256) void k_copy_image(const uint4* __restrict__ src, uint4* __restrict__ dst, const uint32_t n) {
-  for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) dst[i] = src[i];
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) dst[i] = src[i];
 }
 
 }  // namespace
@@ -1987,10 +1987,9 @@ hipError_t launch_copy_image(const void* src, void* dst, size_t bytes, hipStream
   uint4* to = (uint4*)dst;
   uint32_t n = (uint32_t)(bytes / 16);
   if (n == 0) return hipSuccess;
-  const uint32_t wg = (n + 255) / 256;
   void* args[3] = {&from, &to, &n};
   // (the launch's own status: the thread's last error may be an older one of the caller's)
-  return hipLaunchKernel((const void*)k_copy_image, dim3(wg < 64 ? wg : 64), dim3(256), args, 0, st);
+  return hipLaunchKernel((const void*)k_copy_image, dim3((n + 255) / 256), dim3(256), args, 0, st);
 }
 
 // ------------------------------------------------------------------------------------------
