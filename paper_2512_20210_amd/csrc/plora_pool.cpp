@@ -226,10 +226,14 @@ constexpr int kMinTokens[2] = {16, 64};
 constexpr int kF32MinTokens = 16;  // (fp32 pools, both)
 // ... in fp32 shrink only in a batch of at least this many such items; its launches then decide, see f32_pays.
 constexpr int64_t kF32MinItems = 64;
-// Batch images up to this size go by a kernel.  One projection of 16 tokens takes 21 us a step that way and 43 with the
-// side stream, a prefill of 5,120 tokens 131 either way, and 161 against 183 when the step starts on an idle GPU.  A
-// larger image is better copied behind running kernels (1,024 tokens over 1,000 adapters, about 256 KiB: 722
-// against 718 us).
+// Batch images up to this size go by a kernel on the batch's stream, larger ones by a copy on the side stream.  A step that starts on
+// an idle GPU gains 16 - 20 us by the kernel at every size (4 - 370 KiB: 46 -> 28 us a step of one 1024 -> 1024 projection, 903 -> 883 of 4,096
+// tokens over 500 adapters), and so does a stream of steps that the host bounds (38 -> 18, 79 -> 60 at 192 KiB).  In a stream
+// of steps that the GPU bounds the copy runs behind the last step's kernels, and the kernel's reading of host memory does
+// not: us a step by side stream / by kernel, medians of ten alternating runs, 4 slots 4096 -> 4096: 53 KiB 59.6 / 50.6, 66 KiB 65.3 / 61.9,
+// 73 KiB 155.5 / 149.4, 84 KiB 74.6 / 79.7, 99 KiB 98.6 / 99.0, 118 KiB 237.9 / 232.8, 125 KiB 110.6 / 116.9, 149 KiB 119.0 / 127.4, 248 KiB
+// 264.6 / 273.7; 16 slots 2048 -> 2048: 68 KiB 179.3 / 179.7, 197 KiB 468 / 473, 339 KiB 724 / 736, 367 KiB 795 / 807.  So up to 66 KiB the kernel is
+// ahead either way, from some 140 KiB on it costs such a stream 1 - 8 %, and between the two are even.
 constexpr size_t kImageByKernel = (size_t)128 << 10;
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
