@@ -252,10 +252,11 @@ int plora_pool_stats(plora_pool* pool, plora_stats* out);
  * workgroups of 512 columns is issued with one workgroup per 256 columns instead (twice as many, each
  * half as long; v is then read twice as often), which is faster while the launch is too short to hide
  * a workgroup's chain of loads behind other workgroups; 0 = never.  Results do not depend on it.
- * "mfma_shrink_depth" (0, 1 or 2; default 0): runs of 64 values of the contraction that a matrix-core
- * shrink item keeps in flight per wavefront; 0 lets the library choose per launch (2 when the batch's
- * matrix-core token tiles are at least half full on average, as in prefill, when a slot of the launch
- * has d_in > 4096, or when the launch has at most 2500 workgroups; else 1).  Results do not depend on it.
+ * "mfma_shrink_depth" (0, 1 or 2; default 0): runs of the contraction, 128 bytes of a row each, that a matrix-core
+ * shrink item of 32 x 32 keeps in flight per wavefront (always 2 in a launch that takes tiles of 64 x 64 besides); 0 lets
+ * the library choose per launch (2 when the batch's matrix-core token tiles are at least half full on average, as in
+ * prefill, when a slot of the launch has d_in > 4096, or when the launch has at most 2500 workgroups; else 1).  Results
+ * do not depend on it.
  * "contig_fast_path" (0 or 1, default 1; for adapters loaded afterwards): an adapter whose pages are
  * physically consecutive is handed to the kernels by its first page instead of its page table (no table
  * entries in the batch's image, one dependent read less at the head of every work item); 0 treats every
