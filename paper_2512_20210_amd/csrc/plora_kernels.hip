@@ -661,8 +661,8 @@ __device__ __forceinline__ void shrink_mfma4_body(const LaunchArgs& a, const Ite
   auto multiply = [&]() {
     if constexpr (DT == 2) {
       // Tiles without tokens or rows are left out (fp32 products are what bounds an item of few adapters' groups).
-      // 16 products at a time, collected by additions: one chain over d_in / 4 products would have 2.6 times the
-      // error of the vector-ALU item's short ones (at d_in 2048 4.1e-7 of the 2-norm against 1.2e-7).
+      // 16 products at a time, collected by additions: one chain over d_in / 4 products would have 3.4 times the
+      // error of the vector-ALU item's short ones (at d_in 2048 4.1e-7 of the 2-norm against 1.2e-7; this way 1.2e-7).
       uint4 xo[2][2];
 #pragma unroll
       for (int t = 0; t < 2; ++t)
@@ -789,7 +789,7 @@ __device__ __forceinline__ void shrink_mfma4_body(const LaunchArgs& a, const Ite
 
 // shrink, panel item (batches with many large groups: prefill): up to 64 rows of A x up to 64 tokens by a workgroup
 // whose four wavefronts share every tile, which goes from memory to LDS without a stop in registers.
-// What bounds it: the split item above (32 x 32) asks the CU's L1 for 2.5 KiB per 1024 products, and x comes back from
+// What bounds it: the split item above (32 x 32) asks the CU's L1 for 128 bytes per 1024 products (this one: 64), and x comes back from
 // the last-level cache once per 32 rows of A and slot: a prefill of 5,120 tokens through q, k, v, o
 // (4096 -> 4096, ranks 8 .. 128) asked L1 for 644 MB, 250 MB of them past L2, and took 53.5 us (mean of three
 // batches).  The larger tile asks for 358 MB; with the slots of a token tile side by side on one XCD (k_shrink_panel)
