@@ -1416,10 +1416,15 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     // what a panel batch has besides (decode tokens in a batch with prefill) is as often too little to fill the GPU
     const bool light_coop = panel && n_all > b->n_heavy[op] && coop_max > 0 && b->n_items[1][2] > 0 &&
                             (int64_t)nq * ((n_all - b->n_heavy[op]) / 4) * chunks <= coop_max;
-    const Part parts[2] = {{list, panel ? b->n_heavy[op] : n_all, panel ? panel_mode : coop ? kModeCoop : panel_shrink && !cut ? kModeShrinkPanel : deep ? kModeDeep
-                           : is_shrink && p->dtype == PLORA_F32 && (cut || b->n_heavy[0] == 0) ? kModeLight : kModeBlocks},
-                           light_coop ? Part{(const ItemRec*)(b->d_img + b->off_items[1][2]), b->n_items[1][2], kModeCoop}
-                                      : Part{list + b->n_heavy[op], panel ? n_all - b->n_heavy[op] : 0, kModeBlocks}};
+    int mode = kModeBlocks;
+    if (panel) mode = panel_mode;
+    else if (coop) mode = kModeCoop;
+    else if (panel_shrink && !cut) mode = kModeShrinkPanel;
+    else if (deep) mode = kModeDeep;
+    else if (is_shrink && p->dtype == PLORA_F32 && (cut || b->n_heavy[0] == 0)) mode = kModeLight;
+    Part parts[2] = {{list, panel ? b->n_heavy[op] : n_all, mode}, {nullptr, 0, kModeBlocks}};
+    if (light_coop) parts[1] = Part{(const ItemRec*)(b->d_img + b->off_items[1][2]), b->n_items[1][2], kModeCoop};
+    else if (panel) parts[1] = Part{list + b->n_heavy[op], n_all - b->n_heavy[op], kModeBlocks};
     plora_pool::ProfRec rec{op, nullptr, nullptr};
     if (p->profiling) {
       for (hipEvent_t* ev : {&rec.e0, &rec.e1}) {
