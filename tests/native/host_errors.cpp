@@ -21,6 +21,7 @@ hipStream_t g_image_stream = nullptr; // stream of the last one
 long g_fused_runs = 0;
 int g_items[2][4];                    // [op][kind]: records that the launches read
 int g_shrink_mode = -1, g_shrink_lone = 0;  // of the last launch
+std::vector<std::pair<int, std::vector<int32_t>>> g_rest;  // cooperative expand launches: an item's rank, and the head of the page table it gives
 }  // namespace
 
 namespace plora {
@@ -43,8 +44,15 @@ hipError_t launch_shrink(int dtype, const LaunchArgs& a, const SlotPtrs&, int, i
   count_items(0, a, st);
   return hipSuccess;
 }
-hipError_t launch_expand(int, const LaunchArgs& a, const SlotPtrs&, int, int, int, hipStream_t st, hipEvent_t, hipEvent_t) {
+hipError_t launch_expand(int, const LaunchArgs& a, const SlotPtrs&, int, int, int mode, hipStream_t st, hipEvent_t, hipEvent_t) {
   count_items(1, a, st);
+  if (mode == kModeCoop)
+    fakehip::enqueue_kernel(st, [=] {
+      for (int i = 0; i < a.n_items; ++i) {
+        CHECK(!(a.items[i].kind & kItemContig));
+        g_rest.push_back({a.items[i].rank, std::vector<int32_t>(a.pt + a.items[i].pt_off, a.pt + a.items[i].pt_off + a.items[i].rank)});
+      }
+    });
   return hipSuccess;
 }
 hipError_t launch_scatter(const uint8_t*, uint8_t*, int, uint64_t, const int32_t*, uint32_t, hipStream_t) { return hipSuccess; }
@@ -300,6 +308,44 @@ void fp32_route() {
     CHECK(hipHostFree(blob) == hipSuccess && hipStreamDestroy(st) == hipSuccess);
   }
 }
+// What a panel batch has besides its 64-token blocks goes to the cooperative expand with the page tables of its own adapters, wherever
+// those lie between the adapters of the blocks.
+void rest_tables() {
+  const int32_t d = 1024, ranks[5] = {40, 3, 64, 5, 7}, tokens[5] = {200, 3, 130, 4, 1};
+  plora_layout lay{1, &d, &d, PLORA_BF16, 5, 64};
+  plora_pool* p = nullptr;
+  CHECK(plora_pool_create(4096, 128, &lay, nullptr, 0, &p) == PLORA_OK);  // a page per rank
+  CHECK(plora_pool_set_option(p, "contig_fast_path", 0) == PLORA_OK);
+  CHECK(plora_pool_set_option(p, "panel_min_blocks", 1) == PLORA_OK);
+  hipStream_t st = nullptr;
+  CHECK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess);
+  void* blob = nullptr;
+  CHECK(hipHostMalloc(&blob, plora_adapter_bytes(p, 64), 0) == hipSuccess);
+  std::memset(blob, 0, plora_adapter_bytes(p, 64));
+  std::vector<int32_t> t2a;
+  for (int i = 0; i < 5; ++i) {
+    CHECK(plora_load_adapter(p, i, ranks[i], 1.f, blob, st, nullptr, nullptr) == PLORA_OK);
+    t2a.insert(t2a.end(), (size_t)tokens[i], i);
+  }
+  plora_batch* b = nullptr;
+  CHECK(plora_batch_begin(p, t2a.data(), (int32_t)t2a.size(), st, &b) == PLORA_OK);
+  const float* v = (const float*)0x1000;
+  void* y = (void*)0x10000;
+  g_rest.clear();
+  CHECK(plora_expand(p, b, 0, 1, &v, &y, st) == PLORA_OK);
+  CHECK(plora_batch_end(p, b) == PLORA_OK);
+  fakehip::drain();
+  CHECK(g_rest.size() == 3);  // adapters 4, 3 and 1, longest first
+  for (int k = 0; k < 3; ++k) {
+    const int i = k == 0 ? 4 : k == 1 ? 3 : 1;
+    const int32_t* pt = nullptr;
+    uint32_t n = 0;
+    CHECK(plora_adapter_pages(p, i, &pt, &n) == PLORA_OK && n == (uint32_t)ranks[i]);
+    CHECK(g_rest[k].first == ranks[i] && g_rest[k].second == std::vector<int32_t>(pt, pt + n));
+  }
+  CHECK(plora_pool_destroy(p) == PLORA_OK);
+  CHECK(hipHostFree(blob) == hipSuccess && hipStreamDestroy(st) == hipSuccess);
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -311,6 +357,7 @@ int main(int argc, char** argv) {
     else if (name == "fp32_thresholds") fp32_thresholds();
     else if (name == "panel_route") panel_route();
     else if (name == "fp32_route") fp32_route();
+    else if (name == "rest_tables") rest_tables();
     else return 2;
     std::printf("%s OK\n", name.c_str());
   }

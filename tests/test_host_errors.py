@@ -24,7 +24,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["image_in_flight", "callers_error", "counters_cleared", "fp32_thresholds", "panel_route", "fp32_route"])
+@pytest.mark.parametrize("check", ["image_in_flight", "callers_error", "counters_cleared", "fp32_thresholds", "panel_route", "fp32_route", "rest_tables"])
 def test_batch_begin(exe, check):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0", UBSAN_OPTIONS="print_stacktrace=1")
     r = subprocess.run([exe, check], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120, env=env)
