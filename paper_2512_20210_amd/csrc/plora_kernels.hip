@@ -1658,9 +1658,9 @@ __device__ __forceinline__ void shrink_coop_body(const LaunchArgs& a, const Item
   }
 }
 
-// TWO: items of one or two tokens keep two chunks in flight.  For launches that leave a CU one workgroup at most (4 tokens
-// through 32 layers in calls of 3 and 1 slots, 7 - 21 workgroups: 693 -> 613 us a step); larger ones lose more by the
-// registers (four instead of five workgroups fit a CU: 101 tokens, 532 workgroups, 649 against 653).
+// TWO: items of one or two tokens keep two chunks in flight.  For launches that leave a CU one workgroup at most (4 tokens through
+// d_in 4096, 21 and 7 workgroups: 6.4 and 6.2 -> 5.3 and 5.0 us a launch); larger ones lose more by the registers
+// (four instead of five workgroups fit a CU: 101 tokens, 32 launches of 532 workgroups, 649 against 653 us a step).
 template <int DT, bool TWO>
 __global__ __launch_bounds__(256) void k_shrink_coop(const LaunchArgs a, const SlotPtrs p) {
   __shared__ int32_t lds_pt[kPtWindow / 4];
