@@ -74,20 +74,42 @@ class Case:
         assert pt_g.tolist() == pt_o.tolist(), "page tables differ for adapter %d" % i
         return pt_g
 
+    @classmethod
+    def scattered(cls, oracle_mod, layout, ranks, scales, page_bytes, seed, max_rank=None):
+        """The adapters of `ranks` on pages that are not consecutive: the pool is first filled with adapters of rank 1, every second of
+        which leaves.  An adapter larger than those gets pages in several places; one that is not is handed to the
+        kernels by its page table all the same (contig_fast_path 0)."""
+        elt = 4 if layout.dtype == DT_F32 else 2
+        per_rank = elt * (sum(layout.d_in) + sum(layout.d_out))
+        small = -(-per_rank // page_bytes)
+        holes = sum(-(-r * per_rank // page_bytes) for r in ranks) // small + 1
+        n = len(ranks)
+        fill = range(n, n + 2 * holes)
+        case = cls(oracle_mod, layout, list(ranks) + [1] * len(fill), list(scales) + [1.0] * len(fill), page_bytes, small * len(fill), seed,
+                   max_rank=max_rank or max(ranks), load_order=fill)
+        for i in fill[::2]:
+            case.evict(i)
+        case.gpool.set_option("contig_fast_path", 0)
+        for i in range(n):
+            pt = case.load(i)
+            assert len(pt) <= small or (np.diff(pt) != 1).any(), "adapter %d lies on consecutive pages" % i
+        return case
+
     def evict(self, i):
         self.opool.evict(i)
         self.gpool.evict(i)
 
-    def run(self, t2a, slots=None, seed=0, y0_zero=False, check=True, x_std=1.0, share_x=(), y0_fill=None):
+    def run(self, t2a, slots=None, seed=0, y0_zero=False, check=True, x_std=1.0, share_x=(), y0_fill=None, xs=None):
         """One batch over `slots` on both sides; returns per-slot dicts with raw outputs.  share_x:
         groups of positions in `slots` (same d_in) that read one x buffer, as q, k, v of a layer do.
-        y0_fill: a raw element value that every entry of y0 takes (e.g. the bit pattern of -0)."""
+        y0_fill: a raw element value that every entry of y0 takes (e.g. the bit pattern of -0).  xs: the slots' raw inputs
+        themselves, in place of drawn ones."""
         torch, lay = self.torch, self.lay
         t2a = np.ascontiguousarray(t2a, dtype=np.int32)
         T = len(t2a)
         slots = list(range(lay.n_slots)) if slots is None else list(slots)
         rng = np.random.default_rng(seed)
-        xs = [make_act(rng, T, lay.d_in[s], lay.dtype, x_std) for s in slots]
+        xs = [make_act(rng, T, lay.d_in[s], lay.dtype, x_std) for s in slots] if xs is None else list(xs)
         for group in share_x:
             for j in group[1:]:
                 assert lay.d_in[slots[j]] == lay.d_in[slots[group[0]]]

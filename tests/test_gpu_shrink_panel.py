@@ -23,24 +23,24 @@ def _case(oracle_mod, dtype, d_in, ranks, page, limit, scattered=False):
     n = len(d_in)
     lay = Layout(tuple(d_in), (136,) * n, dtype)
     need = sum(-(-(r * 2 * (sum(d_in) + 136 * n)) // page) for r in ranks)
-    case = Case(oracle_mod, lay, ranks, [16.0 / r for r in ranks], page, 2 * need + 8, seed=11, max_rank=max(ranks))
-    if scattered:  # every second adapter leaves, a longer one takes its place: no adapter on consecutive pages
-        for i in range(0, len(ranks), 2):
-            case.evict(i)
-        for i in sorted(range(0, len(ranks), 2), key=lambda k: -ranks[k]):
-            case.load(i)
+    scales = [16.0 / r for r in ranks]
+    if scattered:
+        case = Case.scattered(oracle_mod, lay, ranks, scales, page, seed=11)
+    else:
+        case = Case(oracle_mod, lay, ranks, scales, page, need, seed=11)
     case.kernel_modes = MODES
     case.gpool.set_option("panel_min_tiles_shrink", limit)
     return case
 
 
 @CUT
+@pytest.mark.parametrize("scattered", [False, True], ids=["consecutive", "scattered"])
 @pytest.mark.parametrize("dtype", [DT_BF16, DT_F16])
 @pytest.mark.parametrize("d_in", [64, 128, 192, 1024, 1088, 4096])
-def test_tile_edges(oracle_mod, dtype, d_in, limit):
+def test_tile_edges(oracle_mod, dtype, d_in, scattered, limit):
     ranks = [8, 16, 17, 32, 33, 64, 65, 128, 129, 200]
     groups = [33, 64, 65, 100, 128, 129, 192, 33, 63, 97]
-    case = _case(oracle_mod, dtype, [d_in], ranks, 16384, limit)
+    case = _case(oracle_mod, dtype, [d_in], ranks, 4096 if scattered else 16384, limit, scattered)
     t2a = np.concatenate([np.full(n, a, np.int32) for a, n in enumerate(groups)] + [np.full(5, -1, np.int32)])
     np.random.default_rng(3).shuffle(t2a)
     case.run(t2a, seed=5)
@@ -48,17 +48,17 @@ def test_tile_edges(oracle_mod, dtype, d_in, limit):
 
 
 @CUT
+@pytest.mark.parametrize("dtype", [DT_BF16, DT_F16])
 @pytest.mark.parametrize("page", [4096, 65536])
-def test_scattered_pages_and_shared_x(oracle_mod, page, limit):
+def test_scattered_pages_and_shared_x(oracle_mod, page, dtype, limit):
     ranks = [64, 24, 128, 8, 40, 65]
-    case = _case(oracle_mod, DT_BF16, [1024, 1024, 1024, 512], ranks, page, limit, scattered=True)
+    case = _case(oracle_mod, dtype, [1024, 1024, 1024, 512], ranks, page, limit, scattered=True)
     t2a = np.repeat(np.arange(6, dtype=np.int32), [70, 64, 40, 130, 33, 200])
     np.random.default_rng(4).shuffle(t2a)
     whole = case.run(t2a, seed=6, share_x=[(0, 1, 2)])
     for s in range(4):
-        one = case.run(t2a, slots=[s], seed=6)
-        if s == 0:  # (a lone slot draws the x that slot 0 of the whole call has)
-            assert np.array_equal(one[0]["v_got"], whole[0]["v_got"])
+        one = case.run(t2a, slots=[s], seed=6, xs=[whole[s]["x"]])
+        assert np.array_equal(one[0]["v_got"], whole[s]["v_got"])
     case.close()
 
 

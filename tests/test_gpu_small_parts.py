@@ -29,12 +29,11 @@ def test_rest_of_a_panel_batch(oracle_mod, dtype, scattered):
     ranks = [64, 8, 33, 5, 16, 100]
     lay = Layout((128, 264, 128), (520, 1032, 136), dtype)
     need = sum(-(-(r * 2 * (520 + 1688)) // 4096) for r in ranks)
-    case = Case(oracle_mod, lay, ranks, [16.0 / r for r in ranks], 4096, 2 * need, seed=32, max_rank=101)
-    if scattered:
-        for i in (0, 2, 4):
-            case.evict(i)
-        for i in (2, 0, 4):
-            case.load(i)
+    scales = [16.0 / r for r in ranks]
+    if scattered:  # all of them: the panel blocks' adapters 0 and 5, and the rest's in front of, between and behind those
+        case = Case.scattered(oracle_mod, lay, ranks, scales, 4096, seed=32, max_rank=101)
+    else:
+        case = Case(oracle_mod, lay, ranks, scales, 4096, need, seed=32, max_rank=101)
     # limits that take the cooperative kernel for the rest, the ordinary one, and the library's own
     case.kernel_modes = ((1 << 30, 1, 0, "pair"), (0, 1, 0, "pair"), (2500, 1, 0, "delta"))
     t2a = np.concatenate([np.repeat(np.arange(6, dtype=np.int32), [200, 3, 1, 40, 7, 70]), np.full(4, -1, np.int32)])
