@@ -5,7 +5,7 @@ with eager work and synchronisations between the replays."""
 import numpy as np
 import pytest
 
-from workload import DT_BF16, Layout, draw_tok2adapter, from_elt, make_act
+from workload import DT_BF16, DT_F32, Layout, draw_tok2adapter, from_elt, make_act
 from helpers import TOL_V, TOL_Y, Case, raw_to_torch, rel_err, torch_to_raw
 
 pytestmark = pytest.mark.gpu
@@ -13,14 +13,31 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("mfma", [0, 2])
 def test_captured_step_replays_to_the_eager_result(oracle_mod, mfma):
-    import torch
     lay = Layout((1024, 520), (1024, 264), DT_BF16)
     ranks = [8, 16, 3, 40, 64, 24, 32, 5]
     case = Case(oracle_mod, lay, ranks, [16.0 / r for r in ranks], 16384, 256, seed=41, mfma_min_tokens=mfma)
+    _capture_and_replay(case, draw_tok2adapter(np.random.default_rng(3), 150, np.arange(len(ranks)), s=1.0, none_frac=0.1))
+
+
+# a prefill batch whose shrink takes its 64 x 64 tiles, or the list for launches too small for those; fp32 matrix-core items, or (64 .. 255
+# of them in the batch) the vector-ALU blocks that such launches take in their place
+@pytest.mark.parametrize("dtype,option,value", [(DT_BF16, "panel_min_tiles_shrink", 0), (DT_BF16, "panel_min_tiles_shrink", 1),
+                                                (DT_F32, "mfma_min_tokens", 1), (DT_F32, "coop_max_workgroups_shrink", 0)])
+def test_captured_prefill_replays_to_the_eager_result(oracle_mod, dtype, option, value):
+    lay = Layout((1024, 512), (1024, 264), dtype)
+    ranks = [64, 16, 33, 128, 8]
+    case = Case(oracle_mod, lay, ranks, [16.0 / r for r in ranks], 16384, 256, seed=42)
+    case.gpool.set_option(option, value)
+    t2a = np.repeat(np.array([0, 1, 2, 3, 4, -1], np.int32), [300, 200, 130, 260, 3, 7])
+    np.random.default_rng(4).shuffle(t2a)
+    _capture_and_replay(case, t2a)
+
+
+def _capture_and_replay(case, t2a):
+    import torch
+    lay, T = case.lay, len(t2a)
+    rng = np.random.default_rng(5)
     pool = case.gpool
-    rng = np.random.default_rng(3)
-    T = 150
-    t2a = draw_tok2adapter(rng, T, np.arange(len(ranks)), s=1.0, none_frac=0.1)
     xs = [make_act(rng, T, d, lay.dtype) for d in lay.d_in]
     y0 = [make_act(rng, T, d, lay.dtype) for d in lay.d_out]
     xd = [raw_to_torch(a, "cuda") for a in xs]
