@@ -1392,6 +1392,13 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     const bool cut = is_shrink && b->cut_blocks > 0 && !(panel_shrink ? panel_pays(b, nq, 4 * same >= nq) : f32_pays(b, nq));
     if (coop) layout = 2;
     else if (cut) { layout = 3; a.slot_fastest = 0; }
+    else if (panel_shrink) {
+      // This kernel deals the slots to the XCDs itself, so it takes the dealt list also where the slots are a multiple of 8: the
+      // row panels of a token tile and the token tiles of a group then meet in one L2 (8 slots of own x, 2,048 tokens of
+      // rank 128, d_in 4096: 100 -> 65 us, 73 as split items; 16 slots 195 -> 144, 172).
+      a.slot_fastest = 0;
+      if (p->xcd_remap[0] && b->n_items[0][1] > 0) layout = 1;
+    }
     a.n_lone = layout == 3 ? b->n_lone : 0;
     const ItemRec* list = (const ItemRec*)(b->d_img + b->off_items[op][layout]);
     const int n_all = b->n_items[op][layout];

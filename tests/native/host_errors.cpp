@@ -3,6 +3,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <memory>
 #include <string>
 #include <vector>
@@ -40,6 +41,12 @@ hipError_t launch_shrink(int dtype, const LaunchArgs& a, const SlotPtrs&, int, i
       for (int i = 0; i < a.n_items; ++i) CHECK(a.items[i].kind == -1 || ((a.items[i].kind & 0xff) > 0) == (i < a.n_lone));
       for (int i = 0; i < a.n_lone; ++i) CHECK(a.items[i].kind == -1 || (a.items[i].kind & 0xff) == (dtype == PLORA_F32 ? 3 : 1));
       CHECK(dtype != PLORA_F32 || mode == kModeLight);
+    });
+  if (mode == kModeShrinkPanel)  // block i runs on XCD i % 8, whatever the slots: the row panels of a token tile on one of them
+    fakehip::enqueue_kernel(st, [=] {
+      std::map<int, int> xcd;  // of a tile, by its first token
+      for (int i = 0; i < a.n_items; i += 4)
+        if ((a.items[i].kind & 0xff) == 2) CHECK(xcd.emplace(a.items[i].tok[0], i / 4 % kXcds).first->second == i / 4 % kXcds);
     });
   count_items(0, a, st);
   return hipSuccess;
@@ -233,7 +240,7 @@ void panel_route() {
     {64, 255, 1, 1, 32, kCut}, {64, 256, 1, 1, 32, kPanel}, {16, 256, 1, 1, 32, kCut},
     {64, 63, 4, 4, 32, kCut},  {64, 64, 4, 4, 32, kPanel},  {16, 64, 4, 4, 32, kCut},
     {64, 1, 1, 1, 0, kPanel},  {16, 300, 8, 1, -1, kOther},           {64, 31, 4, 1, 32, kOther},
-    {128, 190, 1, 1, 32, kCut},          {128, 192, 1, 1, 32, kPanel},          {16, 32, 1, 1, 32, kCoop},           {16, 40, 1, 1, 32, kCut},
+    {128, 190, 1, 1, 32, kCut},          {128, 192, 1, 1, 32, kPanel},          {128, 192, 8, 8, 32, kPanel},         {16, 32, 1, 1, 32, kCoop},           {16, 40, 1, 1, 32, kCut},
   };
   for (auto& w : want) {
     const int n_slots = 8;
