@@ -221,9 +221,9 @@ int plora_pool_stats(plora_pool* pool, plora_stats* out);
  * "mfma_min_tokens" / "mfma_min_tokens_expand" (shrink / expand; defaults 16 / 64; 0 = never, 1 =
  * always) or when its work reaches "mfma_min_work" / "mfma_min_work_expand" (defaults 64 / 128; 1 ..
  * 2^30), where work = n * r for shrink and n * r * r / (r rounded up to a multiple of 32) for expand;
- * they take effect for batches begun afterwards.  In fp32 pools the work rule does not apply and both
- * thresholds default to 16, that of shrink only in batches with 64 or more such items of 32 tokens x 32 rows; a threshold
- * that is set holds as it is given, in any batch.  "slot_major" (-1 =
+ * they take effect for batches begun afterwards.  In fp32 pools the work rule does not apply.  A threshold that is set
+ * holds there as it is given, in any batch; unset, expand takes groups of rank 12 or more with at least 32 tokens (or 16, if
+ * n * r reaches 512), and shrink groups of 16, in batches with 64 or more such items of 32 tokens x 32 rows.  "slot_major" (-1 =
  * slots are the fastest grid dimension when their count is a multiple of 8, 0 never, 1 always; for
  * expand also 2 = the 512-column chunks of one work item are the fastest dimension, so that
  * neighbouring workgroups read neighbouring pieces of the same rows of B) and "xcd_remap" (1 = for

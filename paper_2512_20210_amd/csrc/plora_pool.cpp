@@ -223,9 +223,13 @@ int poll_ready(plora_pool* p, Adapter& a) {
 
 // Groups take matrix-core items from this many tokens on, [shrink, expand] ...
 constexpr int kMinTokens[2] = {16, 64};
-constexpr int kF32MinTokens = 16;  // (fp32 pools, both)
+constexpr int kF32MinTokens = 16;  // (fp32 pools, shrink)
 // ... in fp32 shrink only in a batch of at least this many such items; its launches then decide, see f32_pays.
 constexpr int64_t kF32MinItems = 64;
+// fp32 expand takes matrix-core items, unless a threshold is set, by rank and tokens.  Time against that of the vector-ALU items over 512 .. 4,096 tokens, 1 .. 16 slots -> 256 .. 4864: rank 4 and 8
+// 0.92 .. 1.40 (most 1.05 .. 1.3), 9 0.89 .. 1.29; 12 and up with 32 tokens 0.53 .. 1.01; 16, 20 and 24 tokens of rank 16 0.93 .. 1.23, of
+// rank 24 0.83 .. 1.18, of 32 0.72 .. 1.12, of 64 0.61 .. 1.02.
+bool f32_expand_pays(int rank, int32_t n) { return rank >= 12 && (n >= 32 || (n >= 16 && (int64_t)n * rank >= 512)); }
 // Batch images up to this size go by a kernel on the batch's stream, larger ones by a copy on the side stream.  A step that starts on
 // an idle GPU gains 16 - 20 us by the kernel at every size (4 - 370 KiB: 46 -> 28 us a step of one 1024 -> 1024 projection, 903 -> 883 of 4,096
 // tokens over 500 adapters), and so does a stream of steps that the host bounds (38 -> 18, 79 -> 60 at 192 KiB).  In a stream
@@ -1042,11 +1046,11 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
   };
   constexpr int kTokBlock = 128;
   const int min_tokens_s = p->mfma_min_tokens >= 0 ? p->mfma_min_tokens : half ? kMinTokens[0] : kF32MinTokens;
-  const int min_tokens_e = p->mfma_min_tokens_expand >= 0 ? p->mfma_min_tokens_expand : half ? kMinTokens[1] : kF32MinTokens;
+  const int min_tokens_e = p->mfma_min_tokens_expand >= 0 ? p->mfma_min_tokens_expand : kMinTokens[1];
   auto expand_on_matrix_cores = [&](const Adapter& a, int32_t n) {
     const int64_t r32 = ((int64_t)a.rank + 31) / 32 * 32;
     if (min_tokens_e <= 0) return false;
-    if (!half) return n >= min_tokens_e;
+    if (!half) return p->mfma_min_tokens_expand >= 0 ? n >= min_tokens_e : f32_expand_pays(a.rank, n);
     return n >= min_tokens_e || (int64_t)n * a.rank * a.rank >= p->mfma_min_work_expand * r32;
   };
   // How the large groups' expand work is cut: a batch with many 64-token blocks (prefill) keeps them

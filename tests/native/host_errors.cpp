@@ -215,9 +215,9 @@ void counters_cleared() {
 // fp32 pools: an explicit threshold holds as it is given, for each operation by itself; unset, the library's own.
 void fp32_thresholds() {
   struct { int shrink, expand; int64_t tokens; bool mfma_s, mfma_e; } want[] = {
-    {-1, -1, 15, false, false}, {-1, -1, 16, false, true},  // (a lone group is too little for the shrink's)
+    {-1, -1, 31, false, false}, {-1, -1, 32, false, true},  // (a lone group is too little for the shrink's)
     {1, -1, 8, true, false},    {-1, 1, 8, false, true},
-    {32, -1, 31, false, true},  {32, -1, 32, true, true},  {16, -1, 16, true, true},
+    {32, -1, 31, false, false}, {32, -1, 32, true, true},  {16, -1, 16, true, false},
     {-1, 40, 39, false, false}, {-1, 40, 40, false, true}, {0, 0, 48, false, false},
   };
   for (auto& w : want) {
