@@ -278,8 +278,11 @@ void panel_route() {
 void fp32_route() {
   enum { kMatrix, kVector, kCoop };
   struct { int adapters, tokens, rank, slots, set, route; } want[] = {
-    {16, 64, 64, 1, -1, kVector}, {16, 64, 64, 3, -1, kVector}, {16, 64, 64, 4, -1, kMatrix}, {16, 64, 64, 1, 16, kCoop},
-    {64, 16, 8, 2, -1, kCoop},    {64, 16, 8, 4, -1, kMatrix},  {15, 64, 64, 8, -1, kVector},  // (60 items: not in the list)
+    {16, 64, 64, 1, -1, kVector}, {16, 64, 64, 2, -1, kVector}, {16, 64, 64, 3, -1, kMatrix}, {16, 64, 64, 1, 16, kCoop},
+    {64, 16, 8, 2, -1, kCoop},    {64, 16, 8, 4, -1, kVector},  {64, 16, 32, 5, -1, kVector}, {64, 16, 32, 6, -1, kMatrix},
+    {15, 64, 64, 8, -1, kVector},  // (60 items: not in the list, as nothing of rank 8 is)
+    {32, 70, 16, 6, -1, kMatrix}, {32, 70, 16, 1, -1, kVector},  // (the last 6 tokens of a group as vector-ALU items either way)
+    {64, 20, 64, 1, -1, kVector}, {64, 24, 64, 1, -1, kVector},  // (a last block of 4 or 8 tokens has more of the rows)
     {16, 256, 64, 1, -1, kMatrix},
   };
   for (auto& w : want) {
@@ -310,7 +313,10 @@ void fp32_route() {
     std::printf("%d adapters, %d tokens each, rank %d, %d slots: mode %d, %d single records\n", w.adapters, w.tokens, w.rank, w.slots, g_shrink_mode, g_shrink_lone);
     const int route = g_shrink_mode == plora::kModeCoop ? kCoop : g_items[0][1] > 0 ? kMatrix : kVector;
     CHECK(route == w.route);
-    CHECK(route != kVector || w.adapters == 15 || g_items[0][3] == w.adapters * w.tokens / 16 * w.rank / 8);
+    const int rows = w.rank / 8, last = w.tokens % 16, left = w.tokens == 70 ? 6 : 0;  // of a group
+    const int blocks = w.adapters == 15 || w.rank == 8 ? 0 : w.tokens / 16 * rows + (rows * ((last + 3) / 4) + 3) / 4;
+    CHECK(route != kVector || g_items[0][3] == w.adapters * blocks);
+    CHECK(route != kMatrix || g_items[0][0] == (left + 3) / 4 * w.adapters * rows);
     CHECK(plora_pool_destroy(p) == PLORA_OK);
     CHECK(hipHostFree(blob) == hipSuccess && hipStreamDestroy(st) == hipSuccess);
   }
