@@ -223,8 +223,8 @@ int plora_pool_stats(plora_pool* pool, plora_stats* out);
  * 2^30), where work = n * r for shrink and n * r * r / (r rounded up to a multiple of 32) for expand;
  * they take effect for batches begun afterwards.  In fp32 pools the work rule does not apply.  A threshold that is set
  * holds there as it is given, in any batch; unset, expand takes groups of rank 12 or more with at least 32 tokens (or 16, if
- * n * r reaches 512), and shrink whole tiles of 32 tokens x 32 rows and a last one, from half full on, in batches
- * with 64 or more of them.  "slot_major" (-1 =
+ * n * r reaches 512), and shrink groups of 16 in batches with 64 or more such items of 32 tokens x 32 rows, in launches where
+ * they replace enough vector-ALU work.  "slot_major" (-1 =
  * slots are the fastest grid dimension when their count is a multiple of 8, 0 never, 1 always; for
  * expand also 2 = the 512-column chunks of one work item are the fastest dimension, so that
  * neighbouring workgroups read neighbouring pieces of the same rows of B) and "xcd_remap" (1 = for

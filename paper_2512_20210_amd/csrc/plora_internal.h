@@ -19,7 +19,6 @@ constexpr int kMfmaRows = 32;           // rows of A per matrix-core shrink item
 constexpr int kPanelTokS = 64;          // tokens per panel shrink item
 constexpr int kPanelRowsS = 64;         // rows of A per panel shrink item
 constexpr int kPanelKS = 64;            // k-values per step of a panel shrink item: d_in is a multiple of it
-constexpr int kVecBlockTok = 16;        // most tokens of a vector-ALU block given by one record: four items of kValuTok tokens x kShrinkRows rows
 constexpr int kMfmaCols = 128;          // columns of B per matrix-core expand pass
 constexpr int kPtWindow = 1024;         // page-table entries a shrink item may stage in LDS
 constexpr int kMaxRank = 512;           // rows of B an expand item may stage page pairs for (4 KiB of LDS)
@@ -31,12 +30,11 @@ constexpr int kXcds = 8;                // consecutive workgroups go to consecut
 // One wavefront's worth of work, self-contained so that a wavefront needs a single 32-byte read
 // before it can start fetching page-table entries, activations and weights.
 struct ItemRec {
-  int16_t kind;    // -1 = padding (nothing to do), 0 = vector-ALU item, 1 = matrix-core item, 2 = panel shrink item, 3 = block of vector-ALU
-                   // items (shrink; see kVecBlockTok); + kItemOnce if no
+  int16_t kind;    // -1 = padding (nothing to do), 0 = vector-ALU item, 1 = matrix-core item, 2 = panel shrink item; + kItemOnce if no
                    // other item of the batch reads this item's weights (they are then fetched with streaming loads)
   int16_t ntok;    // tokens of the item
   int16_t rank;    // rank of the adapter (0 = tokens without adapter: shrink only clears v)
-  int16_t j0;      // shrink: first row of A (kind 3: first of the block's items, numbered with the token groups innermost);  expand: unused
+  int16_t j0;      // shrink: first row of A;  expand: unused
   float scale;
   int32_t pt_off;  // first entry of the adapter's page table in the batch's table array (kItemContig: first physical page)
   int32_t tok[4];  // vector-ALU item (kValuTok <= 4): the token indices (unused entries repeat the last one);

@@ -1476,22 +1476,6 @@ __global__ __launch_bounds__(256, kWgPerCu) void k_shrink(const LaunchArgs a, co
       return;
     }
   }
-  if constexpr (DT == 2 && DEPTH == 0) {
-    if (item_kind(first) == 3) {
-      // the block's wavefronts take the items j0 .. j0 + 3 of its tokens, token groups innermost
-      const int over = (first.ntok + kValuTok - 1) / kValuTok, item = first.j0 + wave_id();
-      const int t = item % over * kValuTok, j0 = item / over * kShrinkRows;
-      if (j0 >= first.rank) return;
-      ItemRec it = first;
-      it.kind = (int16_t)(first.kind & kItemContig);
-      it.ntok = (int16_t)imin(first.ntok - t, kValuTok);
-      it.j0 = (int16_t)j0;
-#pragma unroll
-      for (int i = 0; i < kValuTok; ++i) it.tok[i] = a.perm[first.tok[0] + t + imin(i, it.ntok - 1)];
-      shrink_valu_item<DT>(a, it, sl, x, v, lds_pt + wave_id() * (kPtWindow / 4));
-      return;
-    }
-  }
   if (lone) return;  // padding
   const int wave = wave_id();
   const ItemRec it = load_item(rec + wave);

