@@ -65,6 +65,7 @@ struct LaunchArgs {
   int32_t log2_page;
   int32_t v_stride;       // = max_rank
   int32_t slot_fastest;   // 1: grid = (slots, items, chunks); 0: grid = (items, chunks, slots); 2 (expand): (chunks, items, slots)
+                          // (k_shrink_panel: 1: slots inside blocks, 0: blocks inside slots)
   int32_t n_slots;        // of the launch (read by k_shrink_panel)
 };
 

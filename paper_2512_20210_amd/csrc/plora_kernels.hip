@@ -1490,11 +1490,12 @@ __global__ __launch_bounds__(256, kWgPerCu) void k_shrink_panel(const LaunchArgs
   __shared__ __align__(16) uint8_t lds[kSpLds];
   __shared__ int32_t lds_pt[kPtWindow], lds_tok[kSpTok];
   auto tile = reinterpret_cast<uint8_t(*)[2][kSmRows * kSmPitch]>(lds);
-  // Workgroup i runs on XCD i % 8.  The workgroups of one block of the list and all slots of the call follow each
-  // other on one XCD: slots that read the same x (q, k, v) then meet its rows in that XCD's L2.  The grid is rounded
-  // up to whole rounds of 8 blocks.
-  const int xcd = blockIdx.x & (kXcds - 1), pair = blockIdx.x / kXcds;
-  const int q = pair % a.n_slots, blk = pair / a.n_slots * kXcds + xcd;
+  // Workgroup i runs on XCD i % 8.  Where slots read the same x (q, k, v), the workgroups of one block of the list and all slots of the call
+  // follow each other on one XCD: they meet the rows of x in that XCD's L2.  Else a slot's blocks do, for the row panels of a
+  // token tile: with the slots in between they find nothing there (32 slots of own x, 5,120 tokens of rank 128, d_in 2048: 409 against 260 us).  The grid is rounded up to whole rounds of 8 blocks.
+  const int xcd = blockIdx.x & (kXcds - 1), pair = blockIdx.x / kXcds, rounds = gridDim.x / kXcds / a.n_slots;
+  const int q = a.slot_fastest ? pair % a.n_slots : pair / rounds;
+  const int blk = (a.slot_fastest ? pair / a.n_slots : pair % rounds) * kXcds + xcd;
   if (4 * blk >= a.n_items) return;
   const SlotRec sl = a.slots[p.slot[q]];
   const uint8_t* x = (const uint8_t*)p.a[q];
@@ -2035,7 +2036,7 @@ hipError_t launch_shrink(int dtype, const LaunchArgs& a0, const SlotPtrs& p, int
   LaunchArgs a = a0;
   const int per = single ? 1 : 4;  // records per workgroup
   const int n_blocks = (a0.n_items - a0.n_lone) / per + a0.n_lone;
-  const int step = a0.slot_fastest ? 65535 : n_blocks;  // grid.z is limited to 65535
+  const int step = a0.slot_fastest && mode != kModeShrinkPanel ? 65535 : n_blocks;  // grid.z is limited to 65535
   for (int first = 0; first < n_blocks; first += step) {
     const int nb = n_blocks - first < step ? n_blocks - first : step;
     a.items = a0.items + per * first;

@@ -1421,10 +1421,10 @@ static int run_slots(plora_pool* p, const plora_batch* b, int32_t slot0, int32_t
     if (coop) layout = 2;
     else if (cut) { layout = 3; if (b->n_lone > 0) a.slot_fastest = 0; }
     else if (panel_shrink) {
-      // This kernel deals the slots to the XCDs itself, so it takes the dealt list also where the slots are a multiple of 8: the
-      // row panels of a token tile and the token tiles of a group then meet in one L2 (8 slots of own x, 2,048 tokens of
-      // rank 128, d_in 4096: 100 -> 65 us, 73 as split items; 16 slots 195 -> 144, 172).
-      a.slot_fastest = 0;
+      // This kernel orders its grid itself and takes the dealt list also where the slots are a multiple of 8: the row panels of a
+      // token tile and the token tiles of a group then meet in one L2 (8 slots of own x, 2,048 tokens of rank 128, d_in 4096:
+      // 100 -> 57 us, 70 as split items; 16 slots 195 -> 136, 162).  Slots that share x side by side, else each by itself.
+      a.slot_fastest = 4 * same >= nq;
       if (p->xcd_remap[0] && b->n_items[0][1] > 0) layout = 1;
     }
     a.n_lone = layout == 3 ? b->n_lone : 0;

@@ -21,7 +21,7 @@ int g_image_checks = 0;               // image kernels that have run
 hipStream_t g_image_stream = nullptr; // stream of the last one
 long g_fused_runs = 0;
 int g_items[2][4];                    // [op][kind]: records that the launches read
-int g_shrink_mode = -1, g_shrink_lone = 0;  // of the last launch
+int g_shrink_mode = -1, g_shrink_lone = 0, g_shrink_shared = 0;  // of the last launch
 std::vector<std::pair<int, std::vector<int32_t>>> g_rest;  // cooperative expand launches: an item's rank, and the head of the page table it gives
 }  // namespace
 
@@ -42,6 +42,7 @@ hipError_t launch_shrink(int dtype, const LaunchArgs& a, const SlotPtrs&, int, i
       CHECK(dtype != PLORA_F32);
       for (int i = 0; i < a.n_lone; ++i) CHECK(a.items[i].kind == -1 || (a.items[i].kind & 0xff) == 1);
     });
+  g_shrink_shared = a.slot_fastest;
   if (mode == kModeShrinkPanel)  // block i runs on XCD i % 8, whatever the slots: the row panels of a token tile on one of them
     fakehip::enqueue_kernel(st, [=] {
       std::map<int, int> xcd;  // of a tile, by its first token
@@ -269,6 +270,7 @@ void panel_route() {
                 g_shrink_lone);
     const int route = g_shrink_mode == plora::kModeShrinkPanel ? kPanel : g_shrink_mode == plora::kModeCoop ? kCoop : g_shrink_lone > 0 ? kCut : kOther;
     CHECK(route == w.route);
+    CHECK(route != kPanel || g_shrink_shared == (4 * (w.slots - w.distinct_x) >= w.slots));  // slots that read one x side by side
     CHECK(plora_pool_destroy(p) == PLORA_OK);
     CHECK(hipHostFree(blob) == hipSuccess && hipStreamDestroy(st) == hipSuccess);
   }
